@@ -10,27 +10,24 @@
 //   sha256_midstates_split: the same for few keys of several blocks, a
 //                     workgroup of two waves per four keys (one per
 //                     16-lane row), the schedules on the second wave;
-//   sha256_chain:     two lanes per sequence, run the final compression of
-//                     each key in order, feeding key_{i-1} in as message
-//                     words 0..7 (the serial part: one compression per key);
+//   sha256_chain_split: the final compression of each key in order, feeding
+//                     key_{i-1} in as message words 0..7 (the serial part:
+//                     one compression per key), for few long chains: a
+//                     workgroup of two waves per four sequences (one per
+//                     16-lane row), rounds on one wave and the message
+//                     schedule on the other;
+//   sha256_chain_pair_split: the same with two lanes per sequence, 64
+//                     sequences per workgroup of four waves;
 //   sha256_chain_lane: the same with one lane per sequence, for batches of
-//                     sequences large enough to give every SIMD more than
-//                     one wave of the two-lane form;
-//   sha256_chain_split: the same for few long chains, a workgroup of two
-//                     waves per four sequences (one per 16-lane row), with
-//                     the message schedule moved to the second wave.
+//                     more sequences than that gives every SIMD two waves of.
 // A lone chain runs at the issue rate of one wave, so the instructions per
 // compression set its speed: rotations are v_alignbit_b32, every
 // three-input XOR and Ch/Maj one v_bitop3_b32 (gfx950's three-input logic
-// op), sums v_add3_u32; everything stays in VGPRs (no LDS, no scratch).
-// Splitting the working state and the message schedule over two lanes
-// (below) brings a chained compression to 1,162 instructions from 1,378 in
-// one lane, and gives twice as many waves for a given number of sequences.
-// The split costs lane-instructions (2 x 1,162 per key against 1,378), so
-// once the two-lane form would stack waves on a SIMD the one-lane form
-// finishes first: 65,536 sequences of 16 keys take 47 us in one lane
-// against 66 us in two, while 32,768 of 32 keys (one two-lane wave per
-// SIMD) take 83 us against 72 us.
+// op), sums v_add3_u32.  Splitting the working state over two sides and the
+// schedule onto another wave brings the instructions of a chained
+// compression that are in line to about 700 from 1,378 in one lane.  The
+// split costs lane-instructions, so once its waves would stack up on the
+// SIMDs the one-lane form finishes first.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -133,6 +130,14 @@ __device__ __forceinline__ void parent_words(const uint8_t *parents, int32_t s,
   }
 }
 
+// Word i of the same (i may differ per lane: an index into parent_words'
+// result would move that array out of registers).
+__device__ __forceinline__ uint32_t parent_word(const uint8_t *parents, int32_t s, int i) {
+  if (parents == nullptr) return 0;
+  const uint8_t *p = parents + 32 * (int64_t)s + 4 * i;
+  return ((uint32_t)p[0] << 24) | ((uint32_t)p[1] << 16) | ((uint32_t)p[2] << 8) | (uint32_t)p[3];
+}
+
 // Offsets (Off) are 32-bit when every key and token offset fits, which
 // halves their upload; 64-bit otherwise.
 template <typename Off>
@@ -161,110 +166,6 @@ __global__ __launch_bounds__(256) void sha256_midstates(
   uint4 *out = reinterpret_cast<uint4 *>(mid + 8 * g);
   out[0] = make_uint4(st[0], st[1], st[2], st[3]);
   out[1] = make_uint4(st[4], st[5], st[6], st[7]);
-}
-
-// Two lanes per sequence: lane 2q holds a..d of sequence q's working
-// state, lane 2q+1 holds e..h.  A round is the same instruction stream on
-// both lanes with per-lane rotation amounts: Sigma0(a) and Maj(a, b, c) on
-// the a-side, Sigma1(e) and Ch(e, f, g) on the e-side (Maj(a, b, c) equals
-// Ch(a ^ c, b, c), so one bitop3 serves both); T1 crosses from the e-lane to
-// the a-lane and d from the a-lane to the e-lane through DPP lane moves.
-// The message schedule is split the same way: one step computes W_2j on
-// the e-lane and W_2j+1 on the a-lane, each lane taking the two terms that
-// live on the other lane through a lane swap.
-constexpr int kPermFromE = 0xF5;  // quad_perm [1,1,3,3]: read lane 2q+1
-constexpr int kPermFromA = 0xA0;  // quad_perm [0,0,2,2]: read lane 2q
-constexpr int kPermSwap = 0xB1;   // quad_perm [1,0,3,2]: read the other lane
-constexpr uint32_t kXorAnd = 0x78;  // x ^ (y & z)
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_from(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-}
-
-template <typename Off>
-__global__ __launch_bounds__(64) void sha256_chain(
-    const uint32_t *__restrict__ mid, const Off *__restrict__ key_off,
-    int32_t n_seqs, uint32_t len_bits, const uint8_t *__restrict__ parents,
-    uint8_t *__restrict__ keys) {
-  const int lane = threadIdx.x;
-  const bool e_side = lane & 1;
-  const int32_t s = blockIdx.x * 32 + (lane >> 1);
-  if (s >= n_seqs) return;  // both lanes of a pair leave together
-  const uint32_t r1c = e_side ? 6 : 2, r2c = e_side ? 11 : 13, r3c = e_side ? 25 : 22;
-  const uint32_t m = e_side ? 0u : 0xffffffffu;
-  uint32_t prev[8];
-  parent_words(parents, s, prev);
-  const int64_t k0 = key_off[s], k1 = key_off[s + 1];
-  const uint4 *mh = reinterpret_cast<const uint4 *>(mid);
-  uint4 nx = k0 < k1 ? mh[2 * k0 + (e_side ? 1 : 0)] : make_uint4(0, 0, 0, 0);
-  // Take the first midstate before the loop.  Memory operations complete in
-  // issue order as far as the wait counter is concerned, so a load still
-  // pending at the loop head would make every key wait for the previous
-  // key's store to be acknowledged; with none pending there, a key waits
-  // only for the prefetch of its midstate, issued a whole compression
-  // earlier and ahead of that store.
-  asm volatile("" ::"v"(nx.x), "v"(nx.y), "v"(nx.z), "v"(nx.w));
-  // message words in pairs: x[j] holds W_2j on the e-lane, W_2j+1 on the
-  // a-lane; x[0..3] come from the previous key, x[4..7] are the padding
-  const uint32_t pad8 = e_side ? 0x80000000u : 0u;   // (W8, W9)
-  const uint32_t pad14 = e_side ? 0u : len_bits;      // (W14, W15)
-  uint32_t x[8];
-  {
-    // the parent key: e-lane (W_2j), a-lane (W_2j+1)
-    x[0] = e_side ? prev[0] : prev[1];
-    x[1] = e_side ? prev[2] : prev[3];
-    x[2] = e_side ? prev[4] : prev[5];
-    x[3] = e_side ? prev[6] : prev[7];
-  }
-  for (int64_t k = k0; k < k1; ++k) {
-    const uint4 h0 = nx;  // this lane's half of the midstate
-    if (k + 1 < k1) nx = mh[2 * (k + 1) + (e_side ? 1 : 0)];
-    uint32_t s0 = h0.x, s1 = h0.y, s2 = h0.z, s3 = h0.w;
-    uint32_t X[32];
-    X[0] = x[0]; X[1] = x[1]; X[2] = x[2]; X[3] = x[3];
-    X[4] = pad8; X[5] = 0u; X[6] = 0u; X[7] = pad14;
-#pragma unroll
-    for (int t = 0; t < 64; ++t) {
-      const int j = t >> 1;
-      if ((t & 1) == 0 && j >= 8) {
-        // W_2j (e-lane) and W_2j+1 (a-lane) at once: the partner's terms
-        // come through a lane swap of a register each lane fills for it
-        const uint32_t r1 = e_side ? X[j - 3] : X[j - 4];
-        const uint32_t r2 = e_side ? X[j - 7] : X[j - 8];
-        const uint32_t x1 = X[j - 1];
-        const uint32_t g1 = bitop3<kXor3>(rotr(x1, 17), rotr(x1, 19), x1 >> 10);
-        const uint32_t g0 = bitop3<kXor3>(rotr(r2, 7), rotr(r2, 18), r2 >> 3);
-        X[j] = (g1 + dpp_from<kPermSwap>(g0)) + (X[j - 8] + dpp_from<kPermSwap>(r1));
-      }
-      // W_t on the e-lane: its own word for even t, the a-lane's for odd t
-      const uint32_t wt = (t & 1) ? dpp_from<kPermFromA>(X[j]) : X[j];
-      const uint32_t S = bitop3<kXor3>(__builtin_amdgcn_alignbit(s0, s0, r1c),
-                                       __builtin_amdgcn_alignbit(s0, s0, r2c),
-                                       __builtin_amdgcn_alignbit(s0, s0, r3c));
-      const uint32_t F = bitop3<kCh>(bitop3<kXorAnd>(s0, s2, m), s1, s2);
-      const uint32_t U = S + F;                       // a-lane: T2
-      const uint32_t T1 = U + s3 + (kRound[t] + wt);  // e-lane: T1
-      // the move runs on every lane (a DPP move cannot sit under a branch)
-      const uint32_t dA = dpp_from<kPermFromA>(s3);
-      const uint32_t Q = e_side ? dA : U;
-      const uint32_t nw = dpp_from<kPermFromE>(T1) + Q;
-      s3 = s2; s2 = s1; s1 = s0; s0 = nw;
-    }
-    const uint32_t o0 = h0.x + s0, o1 = h0.y + s1, o2 = h0.z + s2, o3 = h0.w + s3;
-    uint4 *out = reinterpret_cast<uint4 *>(keys + 32 * k + (e_side ? 16 : 0));
-    *out = make_uint4(__builtin_bswap32(o0), __builtin_bswap32(o1), __builtin_bswap32(o2),
-                      __builtin_bswap32(o3));
-    // the key is the next message's words 0..7 (H0..H3 on the a-lane, H4..H7
-    // on the e-lane): x[0] = (H0, H1), x[1] = (H2, H3), x[2] = (H4, H5),
-    // x[3] = (H6, H7) as (e-lane, a-lane)
-    const uint32_t a0 = dpp_from<kPermFromA>(o0), a2 = dpp_from<kPermFromA>(o2);
-    const uint32_t e1 = dpp_from<kPermFromE>(o1), e3 = dpp_from<kPermFromE>(o3);
-    x[0] = e_side ? a0 : o1;
-    x[1] = e_side ? a2 : o3;
-    x[2] = e_side ? o0 : e1;
-    x[3] = e_side ? o2 : e3;
-  }
 }
 
 // One sequence per workgroup of two waves: wave 0 runs the rounds, wave 1
@@ -304,7 +205,7 @@ __global__ __launch_bounds__(64) void sha256_chain(
 // rounds 43..63, the key into LDS; a barrier, after which the schedule
 // wave reads the key, stores the previous one and starts the next key's
 // words.  Each wave runs its own loop with the same four barriers per key.
-#define EA_RND(S0, S1, S2, K, VI, VO, NW)                                                    \
+#define EA_RND(SH, S0, S1, S2, K, VI, VO, NW)                                                    \
   "v_alignbit_b32 %[r1], %[" S0 "], %[" S0 "], %[c1]\n\t"                                    \
   "v_alignbit_b32 %[r2], %[" S0 "], %[" S0 "], %[c2]\n\t"                                    \
   "v_alignbit_b32 %[r3], %[" S0 "], %[" S0 "], %[c3]\n\t"                                    \
@@ -312,12 +213,12 @@ __global__ __launch_bounds__(64) void sha256_chain(
   "v_bitop3_b32 %[F], %[x], %[" S1 "], %[" S2 "] bitop3:0xca\n\t"                            \
   "v_bitop3_b32 %[S], %[r1], %[r2], %[r3] bitop3:0x96\n\t"                                   \
   "v_add3_u32 %[G], %[S], %[F], %[" VI "]\n\t"                                               \
-  "v_add_u32_dpp %[P], %[" S2 "], %[" K "] row_shr:12 row_mask:0xf bank_mask:0xf "           \
+  "v_add_u32_dpp %[P], %[" S2 "], %[" K "] row_shr:" SH " row_mask:0xf bank_mask:0xf "           \
   "bound_ctrl:1\n\t"                                                                         \
   "v_xad_u32 %[" VO "], %[" S2 "], %[m], %[P]\n\t"                                           \
-  "v_add_u32_dpp %[" NW "], %[G], %[G] row_shl:12 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+  "v_add_u32_dpp %[" NW "], %[G], %[G] row_shl:" SH " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
 // The last round of a compression: no next V, two wait states instead.
-#define EA_RND_LAST(S0, S1, S2, VI, NW)                                                      \
+#define EA_RND_LAST(SH, S0, S1, S2, VI, NW)                                                      \
   "v_alignbit_b32 %[r1], %[" S0 "], %[" S0 "], %[c1]\n\t"                                    \
   "v_alignbit_b32 %[r2], %[" S0 "], %[" S0 "], %[c2]\n\t"                                    \
   "v_alignbit_b32 %[r3], %[" S0 "], %[" S0 "], %[c3]\n\t"                                    \
@@ -326,7 +227,7 @@ __global__ __launch_bounds__(64) void sha256_chain(
   "v_bitop3_b32 %[S], %[r1], %[r2], %[r3] bitop3:0x96\n\t"                                   \
   "v_add3_u32 %[G], %[S], %[F], %[" VI "]\n\t"                                               \
   "s_nop 1\n\t"                                                                              \
-  "v_add_u32_dpp %[" NW "], %[G], %[G] row_shl:12 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+  "v_add_u32_dpp %[" NW "], %[G], %[G] row_shl:" SH " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
 
 // Per-lane constants of the split round: rotation amounts and the side mask.
 struct SplitLane {
@@ -337,56 +238,63 @@ struct SplitState {
   uint32_t s0, s1, s2, s3, v;
 };
 
-// Four rounds; k0..k3 are K + W of the round after each (1 on a-lanes).
-__device__ __forceinline__ void split_rounds4(SplitState &q, uint32_t k0, uint32_t k1,
-                                              uint32_t k2, uint32_t k3, const SplitLane &c) {
-  uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, v2, vo, n0, n1, n2, n3;
-  asm volatile(EA_RND("s0", "s1", "s2", "k0", "V", "v0", "n0")
-               EA_RND("n0", "s0", "s1", "k1", "v0", "v1", "n1")
-               EA_RND("n1", "n0", "s0", "k2", "v1", "v2", "n2")
-               EA_RND("n2", "n1", "n0", "k3", "v2", "Vo", "n3")
-               : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x), [F] "=&v"(F),
-                 [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0), [v1] "=&v"(v1),
-                 [v2] "=&v"(v2), [Vo] "=&v"(vo), [n0] "=&v"(n0), [n1] "=&v"(n1),
-                 [n2] "=&v"(n2), [n3] "=&v"(n3)
-               : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v), [k0] "v"(k0),
-                 [k1] "v"(k1), [k2] "v"(k2), [k3] "v"(k3), [c1] "v"(c.c1), [c2] "v"(c.c2),
-                 [c3] "v"(c.c3), [m] "v"(c.m));
-  q.s0 = n3; q.s1 = n2; q.s2 = n1; q.s3 = n0; q.v = vo;
-}
-// Three rounds.
-__device__ __forceinline__ void split_rounds3(SplitState &q, uint32_t k0, uint32_t k1,
-                                              uint32_t k2, const SplitLane &c) {
-  uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, vo, n0, n1, n2;
-  asm volatile(EA_RND("s0", "s1", "s2", "k0", "V", "v0", "n0")
-               EA_RND("n0", "s0", "s1", "k1", "v0", "v1", "n1")
-               EA_RND("n1", "n0", "s0", "k2", "v1", "Vo", "n2")
-               : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x), [F] "=&v"(F),
-                 [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0), [v1] "=&v"(v1),
-                 [Vo] "=&v"(vo), [n0] "=&v"(n0), [n1] "=&v"(n1), [n2] "=&v"(n2)
-               : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v), [k0] "v"(k0),
-                 [k1] "v"(k1), [k2] "v"(k2), [c1] "v"(c.c1), [c2] "v"(c.c2), [c3] "v"(c.c3),
-                 [m] "v"(c.m));
-  q.s3 = q.s0; q.s0 = n2; q.s1 = n1; q.s2 = n0; q.v = vo;
-}
-// Rounds 62 and 63 (the last): k0 is K + W of round 63.
-__device__ __forceinline__ void split_rounds_end(SplitState &q, uint32_t k0,
-                                                 const SplitLane &c) {
-  uint32_t r1, r2, r3, x, F, S, G, P, v0, n0, n1;
-  asm volatile(EA_RND("s0", "s1", "s2", "k0", "V", "v0", "n0")
-               EA_RND_LAST("n0", "s0", "s1", "v0", "n1")
-               : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x), [F] "=&v"(F),
-                 [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0), [n0] "=&v"(n0),
-                 [n1] "=&v"(n1)
-               : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v), [k0] "v"(k0),
-                 [c1] "v"(c.c1), [c2] "v"(c.c2), [c3] "v"(c.c3), [m] "v"(c.m));
-  q.s3 = q.s1; q.s2 = q.s0; q.s1 = n0; q.s0 = n1;
-}
+// The rounds in blocks, for a row shift of SH lanes between the sides:
+// NAME##4 four rounds (k0..k3 are K + W of the round after each, 1 on
+// a-lanes), NAME##3 three, NAME##_end rounds 62 and 63 (k0 of round 63).
+#define EA_SPLIT_ROUNDS(NAME, SH)                                                            \
+  __device__ __forceinline__ void NAME##4(SplitState &q, uint32_t k0, uint32_t k1,           \
+                                          uint32_t k2, uint32_t k3, const SplitLane &c) {    \
+    uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, v2, vo, n0, n1, n2, n3;                      \
+    asm volatile(EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
+                 EA_RND(SH, "n0", "s0", "s1", "k1", "v0", "v1", "n1")                        \
+                 EA_RND(SH, "n1", "n0", "s0", "k2", "v1", "v2", "n2")                        \
+                 EA_RND(SH, "n2", "n1", "n0", "k3", "v2", "Vo", "n3")                        \
+                 : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
+                   [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
+                   [v1] "=&v"(v1), [v2] "=&v"(v2), [Vo] "=&v"(vo), [n0] "=&v"(n0),           \
+                   [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3)                            \
+                 : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v),             \
+                   [k0] "v"(k0), [k1] "v"(k1), [k2] "v"(k2), [k3] "v"(k3), [c1] "v"(c.c1),   \
+                   [c2] "v"(c.c2), [c3] "v"(c.c3), [m] "v"(c.m));                            \
+    q.s0 = n3; q.s1 = n2; q.s2 = n1; q.s3 = n0; q.v = vo;                                    \
+  }                                                                                          \
+  __device__ __forceinline__ void NAME##3(SplitState &q, uint32_t k0, uint32_t k1,           \
+                                          uint32_t k2, const SplitLane &c) {                 \
+    uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, vo, n0, n1, n2;                              \
+    asm volatile(EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
+                 EA_RND(SH, "n0", "s0", "s1", "k1", "v0", "v1", "n1")                        \
+                 EA_RND(SH, "n1", "n0", "s0", "k2", "v1", "Vo", "n2")                        \
+                 : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
+                   [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
+                   [v1] "=&v"(v1), [Vo] "=&v"(vo), [n0] "=&v"(n0), [n1] "=&v"(n1),           \
+                   [n2] "=&v"(n2)                                                            \
+                 : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v),             \
+                   [k0] "v"(k0), [k1] "v"(k1), [k2] "v"(k2), [c1] "v"(c.c1),                 \
+                   [c2] "v"(c.c2), [c3] "v"(c.c3), [m] "v"(c.m));                            \
+    q.s3 = q.s0; q.s0 = n2; q.s1 = n1; q.s2 = n0; q.v = vo;                                  \
+  }                                                                                          \
+  __device__ __forceinline__ void NAME##_end(SplitState &q, uint32_t k0,                     \
+                                             const SplitLane &c) {                           \
+    uint32_t r1, r2, r3, x, F, S, G, P, v0, n0, n1;                                          \
+    asm volatile(EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
+                 EA_RND_LAST(SH, "n0", "s0", "s1", "v0", "n1")                               \
+                 : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
+                   [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
+                   [n0] "=&v"(n0), [n1] "=&v"(n1)                                            \
+                 : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v),             \
+                   [k0] "v"(k0), [c1] "v"(c.c1), [c2] "v"(c.c2), [c3] "v"(c.c3),             \
+                   [m] "v"(c.m));                                                            \
+    q.s3 = q.s1; q.s2 = q.s0; q.s1 = n0; q.s0 = n1;                                          \
+  }
+EA_SPLIT_ROUNDS(split_rounds, "12")
+EA_SPLIT_ROUNDS(pair_rounds, "8")
 
 // DPP move within a row of 16 lanes; lanes whose source lies outside the
 // row read zero.
 constexpr int kRowShl1 = 0x101, kRowShl9 = 0x109, kRowShl14 = 0x10E;
-constexpr int kRowShr2 = 0x112, kRowShr7 = 0x117, kRowShr12 = 0x11C, kRowShr15 = 0x11F;
+constexpr int kRowShr2 = 0x112, kRowShr7 = 0x117, kRowShr8 = 0x118, kRowShr12 = 0x11C,
+              kRowShr15 = 0x11F;
+constexpr int kRowRor8 = 0x128;  // lanes j and j + 8 of a row swap
 template <int CTRL>
 __device__ __forceinline__ uint32_t row_move(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
@@ -553,10 +461,7 @@ __global__ __launch_bounds__(128) void sha256_chain_split(
     // read per lane rather than from prev[j], which a per-lane index would
     // move out of registers
     uint32_t wp = j == 8 ? 0x80000000u : (j == 15 ? len_bits : 0u);
-    if (j < 8 && parents != nullptr && s < n_seqs) {
-      const uint8_t *pw = parents + 32 * (int64_t)s + 4 * j;
-      wp = ((uint32_t)pw[0] << 24) | ((uint32_t)pw[1] << 16) | ((uint32_t)pw[2] << 8) | pw[3];
-    }
+    if (j < 8 && s < n_seqs) wp = parent_word(parents, s, j);
     const uint32_t kp0 = kRound[16 + j], kp1 = kRound[32 + j], kp2 = kRound[48 + j];
     uint32_t *kw_row = lds + kSpKw + 48 * row;
     for (Off kk = 0; kk < kmax; ++kk) {
@@ -579,6 +484,196 @@ __global__ __launch_bounds__(128) void sha256_chain_split(
     // stored theirs in the loop
     if (len > 0 && len == kmax && j < 8)
       reinterpret_cast<uint32_t *>(keys + 32 * (k1 - 1))[j] = __builtin_bswap32(wp);
+  }
+}
+
+// Two lanes per sequence, for batches of more chains than the row form above
+// spreads over the chip: workgroups of four waves carry 64 chains, 32 per
+// pair of a rounds wave (0, 2) and a schedule wave (1, 3).  Lane j < 8 of a
+// row is the a-side and lane j + 8 the e-side of chain 8 * row + j of the
+// pair.  The rounds are the same ten instructions with the sides eight lanes
+// apart; the schedule wave uses two lanes per chain: one step gives W_2i on
+// the e-lane and W_2i+1 on the a-lane, each lane taking the two terms that
+// live on the other through a lane swap, 13 instructions for two words.
+//
+// What bounds it is the issue rate of the rounds wave, about 700
+// instructions per key as in the row form, while a wave carries eight times
+// as many chains.  With the rounds and the schedule in one wave (1,150
+// instructions per key, the form before this one) 12,000 ragged chains of up
+// to 125 keys took 322 us of chain kernel, here 203.  Four waves
+// per workgroup rather than two, because a CU puts the second wave of one
+// two-wave workgroup and the first of the next on one SIMD and leaves
+// another empty (read from HW_REG_HW_ID): 16,384 chains of 256 keys took
+// 741 us in whole calls with two-wave workgroups, 627 with these, which fill
+// the four SIMDs.  The schedule waves run at
+// raised priority: where two workgroups share a CU (above 64 chains per CU) a
+// schedule wave has half as much to issue as the other one's rounds wave on
+// its SIMD, which waits for it anyway (18,000 chains of 64 keys 221 us,
+// raised 199; 24,576 of 128 keys 467 and 423).
+//
+// The hand-over goes through two LDS buffers of four words (K + W) per
+// chain: part p = words 16 + 4p .. 19 + 4p is written to buffer p & 1 and
+// published by a barrier; the rounds wave reads it right after, four rounds
+// before its first word is due, and the schedule wave overwrites that
+// buffer only after the next barrier, which the rounds wave reaches with
+// the read done.  The finished key takes both buffers (H0..3, H4..7): the
+// rounds wave has read the last part by then, and the schedule wave reads
+// the key before it writes part 0.
+constexpr int kPpChains = 64;
+constexpr int kPpThreads = 256;
+constexpr int kPpParts = 12;
+constexpr int kPpBuf = 4 * kPpChains;  // 32-bit words of one buffer
+constexpr int kPpOnes = 2 * kPpBuf;    // four ones: the a-lanes' K + W
+constexpr int kPpWords = kPpOnes + 4;
+
+template <typename Off>
+__global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
+    const uint32_t *__restrict__ mid, const Off *__restrict__ key_off, int32_t n_seqs,
+    uint32_t len_bits, const uint8_t *__restrict__ parents, uint8_t *__restrict__ keys) {
+  __shared__ __align__(16) uint32_t lds[kPpWords];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const bool e_lane = (lane & 8) != 0;
+  const int chain = (wave >> 1) * 32 + (lane >> 4) * 8 + (lane & 7);
+  const int32_t s = (int32_t)blockIdx.x * kPpChains + chain;
+  int64_t k0 = 0, k1 = 0;
+  if (s < n_seqs) {
+    k0 = key_off[s];
+    k1 = key_off[s + 1];
+  }
+  // Both waves run the longest chain's number of keys, so they meet at the
+  // same barriers; a chain past its end computes keys that are never stored.
+  const Off len = (Off)(k1 - k0);
+  Off kmax = len;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const Off o = __shfl_xor(kmax, d, 64);
+    kmax = o > kmax ? o : kmax;
+  }
+  if constexpr (sizeof(Off) == 4) {
+    kmax = (Off)__builtin_amdgcn_readfirstlane((int)kmax);
+  } else {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)kmax);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)kmax >> 32));
+    kmax = (Off)(((uint64_t)hi << 32) | lo);
+  }
+  const uint8_t *par = s < n_seqs ? parents : nullptr;
+  uint4 *slot = reinterpret_cast<uint4 *>(lds) + chain;  // of buffer 0; buffer 1: + kPpChains
+  if ((wave & 1) == 0) {
+    if (wave == 0 && lane < 4) lds[kPpOnes + lane] = 1u;
+    SplitLane c;
+    c.c1 = e_lane ? 6 : 2;
+    c.c2 = e_lane ? 11 : 13;
+    c.c3 = e_lane ? 25 : 22;
+    c.m = e_lane ? 0u : 0xffffffffu;
+    // K_t (t < 8) and K_t + W_t (t = 8..15, the padding) on e-lanes, 1 on a-lanes
+    uint32_t kc[8], kwc[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) kc[t] = e_lane ? kRound[t] : 1u;
+#pragma unroll
+    for (int t = 8; t < 16; ++t) {
+      const uint32_t w = t == 8 ? 0x80000000u : (t == 15 ? len_bits : 0u);
+      kwc[t - 8] = e_lane ? kRound[t] + w : 1u;
+    }
+    uint32_t o[4];  // the previous key, this lane's half (a: H0..3, e: H4..7)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = parent_word(par, s, e_lane ? 4 + i : i);
+    // midstate of this chain's key k0 + kk, held at the chain's last key past
+    // its end (key 0 for an empty chain: some key exists whenever this runs)
+    const uint4 *mbase =
+        reinterpret_cast<const uint4 *>(mid) + 2 * (len > 0 ? k0 : 0) + (e_lane ? 1 : 0);
+    const Off last = len > 0 ? len - 1 : 0;
+    auto mid_at = [&](Off kk) { return mbase[2 * (int64_t)(kk < last ? kk : last)]; };
+    uint4 nx = make_uint4(0, 0, 0, 0);
+    if (kmax > 0) nx = mid_at(0);
+    // e-lanes read their chain's words, a-lanes the ones; hidden from the
+    // compiler, which would otherwise read both and select
+    uint32_t at0 = e_lane ? 4u * chain : (uint32_t)kPpOnes;
+    uint32_t at1 = e_lane ? 4u * chain + kPpBuf : (uint32_t)kPpOnes;
+    asm volatile("" : "+v"(at0), "+v"(at1));
+    const uint4 *b0 = reinterpret_cast<const uint4 *>(lds + at0);
+    const uint4 *b1 = reinterpret_cast<const uint4 *>(lds + at1);
+    for (Off kk = 0; kk < kmax; ++kk) {
+      const uint4 h0 = nx;
+      if (kk + 1 < kmax) nx = mid_at(kk + 1);
+      SplitState q{h0.x, h0.y, h0.z, h0.w, 0u};
+      uint32_t kw[8];  // K + W of rounds 0..7: the previous key
+#pragma unroll
+      for (int t = 0; t < 4; ++t) kw[t] = row_move<kRowShr8>(o[t]) + kc[t];
+#pragma unroll
+      for (int t = 4; t < 8; ++t) kw[t] = e_lane ? o[t - 4] + kc[t] : 1u;
+      q.v = (q.s3 ^ c.m) + (row_move<kRowShr8>(q.s3) + kw[0]);
+      pair_rounds4(q, kw[1], kw[2], kw[3], kw[4], c);      // rounds 0..3
+      pair_rounds4(q, kw[5], kw[6], kw[7], kwc[0], c);     // 4..7
+      pair_rounds4(q, kwc[1], kwc[2], kwc[3], kwc[4], c);  // 8..11
+      __syncthreads();
+      uint4 w = *b0;                                        // words 16..19
+      pair_rounds3(q, kwc[5], kwc[6], kwc[7], c);          // 12..14
+#pragma unroll
+      for (int p = 1; p < kPpParts; ++p) {
+        __syncthreads();
+        const uint4 wn = (p & 1) ? *b1 : *b0;
+        pair_rounds4(q, w.x, w.y, w.z, w.w, c);             // 11 + 4p .. 14 + 4p
+        w = wn;
+      }
+      pair_rounds3(q, w.x, w.y, w.z, c);                    // 59..61
+      pair_rounds_end(q, w.w, c);                           // 62, 63
+      o[0] = h0.x + q.s0; o[1] = h0.y + q.s1; o[2] = h0.z + q.s2; o[3] = h0.w + q.s3;
+      slot[e_lane ? kPpChains : 0] = make_uint4(o[0], o[1], o[2], o[3]);
+      __syncthreads();
+    }
+  } else {
+    // message words in pairs: X[i] holds W_2i on the e-lane, W_2i+1 on the
+    // a-lane; X[0..3] the previous key, X[4..7] the padding
+    __builtin_amdgcn_s_setprio(3);
+    uint32_t kp[24];
+#pragma unroll
+    for (int i = 0; i < 24; ++i) kp[i] = e_lane ? kRound[16 + 2 * i] : kRound[17 + 2 * i];
+    const uint32_t pad8 = e_lane ? 0x80000000u : 0u;  // (W8, W9)
+    const uint32_t pad14 = e_lane ? 0u : len_bits;    // (W14, W15)
+    uint32_t x[4], half[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = parent_word(par, s, e_lane ? 2 * i : 2 * i + 1);
+      half[i] = 0u;
+    }
+    uint32_t *mine = lds + 4 * chain + (e_lane ? 0 : 1);  // words 0, 2 or 1, 3 of a part
+    for (Off kk = 0; kk < kmax; ++kk) {
+      uint32_t X[32];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) X[i] = x[i];
+      X[4] = pad8; X[5] = 0u; X[6] = 0u; X[7] = pad14;
+#pragma unroll
+      for (int p = 0; p < kPpParts; ++p) {
+#pragma unroll
+        for (int i = 8 + 2 * p; i < 10 + 2 * p; ++i) {
+          const uint32_t r1 = e_lane ? X[i - 3] : X[i - 4];
+          const uint32_t r2 = e_lane ? X[i - 7] : X[i - 8];
+          X[i] = (sig1(X[i - 1]) + row_move<kRowRor8>(sig0(r2))) +
+                 (X[i - 8] + row_move<kRowRor8>(r1));
+        }
+        mine[(p & 1) * kPpBuf] = X[8 + 2 * p] + kp[2 * p];
+        mine[(p & 1) * kPpBuf + 2] = X[9 + 2 * p] + kp[2 * p + 1];
+        __syncthreads();
+        // this lane's half of key kk - 1
+        if (p == 0 && kk > 0 && kk <= len)
+          *reinterpret_cast<uint4 *>(keys + 32 * (k0 + (int64_t)kk - 1) + (e_lane ? 16 : 0)) =
+              make_uint4(__builtin_bswap32(half[0]), __builtin_bswap32(half[1]),
+                         __builtin_bswap32(half[2]), __builtin_bswap32(half[3]));
+      }
+      __syncthreads();
+      const uint4 a = slot[0], b = slot[kPpChains];  // H0..3, H4..7
+      x[0] = e_lane ? a.x : a.y; x[1] = e_lane ? a.z : a.w;
+      x[2] = e_lane ? b.x : b.y; x[3] = e_lane ? b.z : b.w;
+      half[0] = e_lane ? b.x : a.x; half[1] = e_lane ? b.y : a.y;
+      half[2] = e_lane ? b.z : a.z; half[3] = e_lane ? b.w : a.w;
+    }
+    // a chain as long as the longest stores its last key here; shorter ones
+    // stored theirs in the loop
+    if (len > 0 && len == kmax)
+      *reinterpret_cast<uint4 *>(keys + 32 * (k1 - 1) + (e_lane ? 16 : 0)) =
+          make_uint4(__builtin_bswap32(half[0]), __builtin_bswap32(half[1]),
+                     __builtin_bswap32(half[2]), __builtin_bswap32(half[3]));
   }
 }
 
@@ -1136,8 +1231,9 @@ void launch_chain(int form, const uint32_t *d_mid, const Off *d_koff, int32_t n_
     hipLaunchKernelGGL(sha256_chain_split<Off>, dim3((n_seqs + kSpRows - 1) / kSpRows),
                        dim3(128), 0, stream, d_mid, d_koff, n_seqs, len_bits, d_parents, d_keys);
   else
-    hipLaunchKernelGGL(sha256_chain<Off>, dim3((n_seqs + 31) / 32), dim3(64), 0, stream, d_mid,
-                       d_koff, n_seqs, len_bits, d_parents, d_keys);
+    hipLaunchKernelGGL(sha256_chain_pair_split<Off>, dim3((n_seqs + kPpChains - 1) / kPpChains),
+                       dim3(kPpThreads), 0, stream, d_mid, d_koff, n_seqs, len_bits, d_parents,
+                       d_keys);
 }
 
 }  // namespace
@@ -1156,16 +1252,18 @@ hipError_t launch_sha256_chain(const uint32_t *d_mid, const void *d_key_offsets,
   }
   if (form == kChainSplit && n_seqs > kMaxSplitGroups) form = kChainPair;  // grid bound
   if (form < 0) {
-    // Up to eight sequences per compute unit (two workgroups of four rows):
-    // the split form, 4-30% less time per call than two lanes per sequence
-    // for chains of 16 to 1,024 keys (1,024 chains of 1,024 keys: 1.55
-    // against 2.15 ms).  At sixteen per compute unit the two-lane form wins
-    // for long chains (its waves hold 32 chains each), beyond for all, and
-    // beyond 128 per compute unit one lane per sequence does.
+    // Up to four sequences per compute unit (one workgroup of four rows): the
+    // row form, whose chains of 256 keys take 363-373 us in a whole call
+    // against 392-427 in the two-lane form; with a second workgroup on each
+    // unit it takes 448-459 us (1,280 to 2,048 chains) against 413-437.  Up
+    // to 128 per unit (two workgroups of the two-lane form) that form: 32,768
+    // chains of 16 / 64 / 128 keys 79 / 257 / 487 us against 86 / 269 / 537
+    // with one lane per sequence; beyond, the one-lane form: 36,000 chains of
+    // 64 keys 286 us against 343.
     int cus = 0;
     const hipError_t e = device_cus(&cus);
     if (e != hipSuccess) return e;
-    form = (int64_t)n_seqs <= 8 * (int64_t)cus
+    form = (int64_t)n_seqs <= 4 * (int64_t)cus
                ? kChainSplit
                : ((int64_t)n_seqs > 128 * (int64_t)cus ? kChainLane : kChainPair);
   }

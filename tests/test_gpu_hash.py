@@ -131,6 +131,25 @@ def test_every_chain_form(form, monkeypatch):
     assert np.array_equal(koffs, okoffs) and np.array_equal(keys, okeys)
 
 
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("n", [1, 8, 31, 32, 33, 63, 64, 65, 200])
+def test_two_lane_form_at_its_workgroup_edges(n, wide, monkeypatch):
+    # 64 chains per workgroup, 32 per pair of waves, 8 per row: part-filled
+    # rows, pairs and workgroups; the longest chain first, last or in between;
+    # empty chains beside it (their lanes run along and store nothing); all
+    # empty but one
+    monkeypatch.setenv("EA_HASH_CHAIN", "pair")
+    if wide:
+        monkeypatch.setenv("EA_HASH_OFFSETS", "64")
+    r = W.rng(300 + n)
+    lengths = [int(x) for x in r.integers(0, 120, size=n)]
+    for at in sorted({0, n // 2, n - 1}):
+        ragged = list(lengths)
+        ragged[at] = 16 * 23 + 5
+        check(ragged, 16, parents=bool(at), seed=301 + n)
+        check([0] * at + [16 * 9] + [0] * (n - 1 - at), 16, parents=True, seed=302 + n)
+
+
 def test_batch_past_the_one_lane_threshold():
     # more sequences than two-lane waves fit one per SIMD (32 per SIMD):
     # the library picks the one-lane chain by itself; ragged lengths, parents;
