@@ -238,6 +238,12 @@ struct SplitState {
   uint32_t s0, s1, s2, s3, v;
 };
 
+// Every instruction of a round is eight bytes long, and each block starts at
+// a multiple of eight: a lone wave is fed by instruction fetch as much as by
+// issue, and instructions that straddle a fetch boundary cost it (a lone
+// 3,500-key chain took 4.89 ms with the blocks where the code before them
+// left them, 4.62 aligned; 32 or 64 bytes cost more in padding than they
+// give: 5.17 and 5.75).
 // The rounds in blocks, for a row shift of SH lanes between the sides:
 // NAME##4 four rounds (k0..k3 are K + W of the round after each, 1 on
 // a-lanes), NAME##3 three, NAME##_end rounds 62 and 63 (k0 of round 63).
@@ -245,7 +251,7 @@ struct SplitState {
   __device__ __forceinline__ void NAME##4(SplitState &q, uint32_t k0, uint32_t k1,           \
                                           uint32_t k2, uint32_t k3, const SplitLane &c) {    \
     uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, v2, vo, n0, n1, n2, n3;                      \
-    asm volatile(EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
+    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
                  EA_RND(SH, "n0", "s0", "s1", "k1", "v0", "v1", "n1")                        \
                  EA_RND(SH, "n1", "n0", "s0", "k2", "v1", "v2", "n2")                        \
                  EA_RND(SH, "n2", "n1", "n0", "k3", "v2", "Vo", "n3")                        \
@@ -261,7 +267,7 @@ struct SplitState {
   __device__ __forceinline__ void NAME##3(SplitState &q, uint32_t k0, uint32_t k1,           \
                                           uint32_t k2, const SplitLane &c) {                 \
     uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, vo, n0, n1, n2;                              \
-    asm volatile(EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
+    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
                  EA_RND(SH, "n0", "s0", "s1", "k1", "v0", "v1", "n1")                        \
                  EA_RND(SH, "n1", "n0", "s0", "k2", "v1", "Vo", "n2")                        \
                  : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
@@ -276,7 +282,7 @@ struct SplitState {
   __device__ __forceinline__ void NAME##_end(SplitState &q, uint32_t k0,                     \
                                              const SplitLane &c) {                           \
     uint32_t r1, r2, r3, x, F, S, G, P, v0, n0, n1;                                          \
-    asm volatile(EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
+    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
                  EA_RND_LAST(SH, "n0", "s0", "s1", "v0", "n1")                               \
                  : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
                    [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
