@@ -62,7 +62,8 @@
  *  EA_XCD_PLACEMENT=index      place work by workgroup index, not by the XCD
  *                              the hardware reports; read at cache creation
  *  EA_GRID_HBM, EA_GRID_GATHER, EA_GRID_SCATTER
- *                              workgroups of the HBM gather (512) / scatter (256)
+ *                              workgroups of the HBM gather / scatter (by
+ *                              default 256 to 1,024, by the copy's size)
  *  EA_HBM_ORDER, EA_GATHER_ORDER, EA_SCATTER_ORDER = entry|layer
  *                              unit order of the HBM gather / scatter: each
  *                              page's layers in turn (entry, the default) or

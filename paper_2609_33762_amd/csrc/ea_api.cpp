@@ -90,10 +90,6 @@ hipError_t host_alloc_retry(void **p, size_t bytes, unsigned flags) {
   return e;
 }
 
-// Workgroups for the HBM-bound kernels, measured best on MI355X (256 CUs):
-// the gather (random reads, sequential writes) peaks with 2 workgroups per
-// CU, the scatter (sequential reads, random writes) with one per CU: more
-// random writes in flight lower its rate.  EA_GRID_HBM sets both.
 // Unit order of the HBM gather / scatter: EA_HBM_ORDER=layer walks every
 // entry of one layer before the next layer; the default walks each page's
 // layers in turn.
@@ -110,10 +106,41 @@ bool hbm_arg_pages() {
   return !(v && std::strcmp(v, "ring") == 0);
 }
 
+// Workgroups of the HBM gather / scatter set by EA_GRID_GATHER,
+// EA_GRID_SCATTER or EA_GRID_HBM (both); 0: chosen by hbm_shape.
 int64_t grid_hbm(int dir) {
   const int both = env_int("EA_GRID_HBM", 0);
-  if (dir == ea::kToSlots) return std::max(1, env_int("EA_GRID_GATHER", both ? both : 512));
-  return std::max(1, env_int("EA_GRID_SCATTER", both ? both : 256));
+  const int v = env_int(dir == ea::kToSlots ? "EA_GRID_GATHER" : "EA_GRID_SCATTER", both);
+  return v > 0 ? v : 0;
+}
+
+// Launch shape of an HBM copy of n pages: workgroups (4 waves each, 256 CUs)
+// and, where parts may be used (page ids in the kernel arguments), whether a
+// (page, layer) piece is cut into parts of a wave each.  Measured on MI355X,
+// microseconds of gather / scatter:
+//  - Up to 112 MiB there are too few whole pieces to fill the chip, or so few
+//    per wave that the last ones run alone: parts of 4 KiB (one round of
+//    loads) on 1,024 workgroups.  8 pages of 32 x 64 KiB 19.8 / 21.1 -> 8.2 /
+//    8.3 (then bound by the host's calls); 48 of them (101 MB) 40.8 / 48.6 ->
+//    36.3 / 40.3; 48 pages of 48 x 32 KiB (75 MB) 33.7 / 37.0 -> 28.0 / 30.6;
+//    200 of 48 x 8 KiB (79 MB) 29.9 / 37.2 -> 29.5 / 31.9.  At 157 MB the
+//    gather of 8 KiB pieces loses (56.6 -> 58.0).
+//  - Pieces of 64 KiB and more: parts of 16 KiB on 512 workgroups at any size
+//    (1,500 pages of 32 x 64 KiB 1,100 / 1,161 -> 1,014 / 1,037); cutting
+//    32 KiB or 40 KiB pieces of large copies loses 2-7%.
+//  - Otherwise whole pieces: the gather (random reads, sequential writes) on
+//    two workgroups per CU, the scatter (sequential reads, random writes) on
+//    one, since more random writes in flight lower its rate, except pieces of
+//    4 KiB or less, which leave too few bytes in flight (2,048 pages of 48 x
+//    4 KiB: 180 us on 256 workgroups, 157 on 512).
+struct HbmShape {
+  int64_t grid;
+  int64_t part_bytes;  // 0: whole pieces
+};
+HbmShape hbm_shape(int dir, int64_t piece, int64_t total, bool parts) {
+  if (parts && total <= (int64_t(112) << 20)) return {1024, piece > 4096 ? 4096 : 0};
+  if (parts && piece >= 65536) return {512, 16384};
+  return {dir == ea::kToSlots || piece <= 4096 ? 512 : 256, 0};
 }
 
 // Host-link kernels: 8 workgroups (32 waves) per direction already reach the
@@ -354,7 +381,8 @@ struct ea_tier {
   EvRec evs[kTransferEvents];
   int64_t seq = 0;                // transfer calls so far
   int64_t bytes_stored = 0, bytes_loaded = 0, store_calls = 0, load_calls = 0;
-  int64_t grid_store = 8, grid_load = 8, grid_layered = 16, grid_gather = 512, grid_scatter = 256;
+  int64_t grid_store = 8, grid_load = 8, grid_layered = 16;
+  int64_t grid_gather = 0, grid_scatter = 0;  // 0: by hbm_shape
   int32_t num_xcd = 1;
   uint32_t xcd_store = 1, xcd_load = 1;
   // loads have priority on the host link when yield_units > 0: load waves
@@ -481,11 +509,29 @@ ea::PieceCopy base_copy(const ea_cache *c, int64_t slot_bytes, int32_t chunk) {
 // entry i goes to slot i / a.chunk): small batches carry their indices in
 // the kernel arguments, and so do the page ids of HBM copies of up to
 // kArgPagesMax pages with identity slots; larger ones go through the index
-// ring.
+// ring.  grid: workgroups (HBM route: 0 = hbm_shape chooses).
 int launch_entries(ea::PieceCopy a, IndexRing &ring, const int64_t *slots,
                    const int32_t *pages, int64_t n, int dir, int route, int64_t grid,
                    hipStream_t s) {
   a.n = n;
+  if (route == ea::kRouteHbm) {
+    // page ids in the arguments and units in entry order: parts may be used
+    const bool parts = !slots && !a.layer_major &&
+                       (n <= ea::kInlineMax || (n <= ea::kArgPagesMax && hbm_arg_pages()));
+    const HbmShape h =
+        hbm_shape(dir, a.piece_bytes, n * a.layer_count * a.piece_bytes, parts);
+    if (grid <= 0) grid = h.grid;
+    if (h.part_bytes > 0) {
+      int32_t shift = 0;
+      while ((h.part_bytes << shift) < a.piece_bytes) ++shift;
+      // equal parts of whole 1 KiB steps of a wave
+      const int64_t each = ((a.piece_bytes >> 4) + (int64_t(1) << shift) - 1) >> shift;
+      if ((n * a.layer_count) << shift <= INT32_MAX) {
+        a.part_shift = shift;
+        a.part_vecs = (int32_t)((each + 63) / 64 * 64);
+      }
+    }
+  }
   if (n <= ea::kInlineMax) {
     ea::InlineIdx inl;
     for (int64_t i = 0; i < n; ++i) {

@@ -58,8 +58,7 @@ __device__ __forceinline__ int64_t unit_layer(const PieceCopy &a, int64_t u, int
 // of layer l inside the slot.
 template <int DIR, bool INLINE, int VEC>
 __device__ __forceinline__ void copy_unit(const PieceCopy &a, int64_t l, int64_t i, int64_t page,
-                                          int64_t slot, int lane) {
-  const int64_t nvec = a.piece_bytes >> 4;
+                                          int64_t slot, int lane, int64_t v0, int64_t nvec) {
   const int64_t c = a.chunk == 1 ? 0 : (int64_t)((uint32_t)i % (uint32_t)a.chunk);
   const int64_t at = l * a.chunk + c;  // piece index inside the slot
   uint8_t *cache_piece = a.cache + (l * a.num_pages + page) * a.piece_bytes;
@@ -71,12 +70,12 @@ __device__ __forceinline__ void copy_unit(const PieceCopy &a, int64_t l, int64_t
   // the host link for a load) overlaps the piece's instead of following it.
   uint64_t *cs = nullptr, *ss = nullptr;
   uint64_t scale = 0;
-  if (a.scales != nullptr) {
+  if (a.scales != nullptr && v0 == 0) {
     cs = reinterpret_cast<uint64_t *>(a.scales + (l * a.num_pages + page) * 8);
     ss = reinterpret_cast<uint64_t *>(slot_base + a.payload_bytes + at * 8);
     if (lane == 0) scale = DIR == kToSlots ? *cs : *ss;
   }
-  for (int64_t base = 0; base < nvec; base += (int64_t)kWave * VEC) {
+  for (int64_t base = v0; base < nvec; base += (int64_t)kWave * VEC) {
     u32x4 r[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
@@ -89,7 +88,7 @@ __device__ __forceinline__ void copy_unit(const PieceCopy &a, int64_t l, int64_t
       if (v < nvec) store_nt(dst + v, r[k]);
     }
   }
-  if (a.scales != nullptr) {
+  if (a.scales != nullptr && v0 == 0) {
     if (lane == 0) {
       if (DIR == kToSlots) *ss = scale; else *cs = scale;
     }
@@ -152,7 +151,8 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
     for (int64_t u = first; u < units; u += waves) {
       const int64_t i = unit_entry(a, u);
       const uint32_t busy = link_busy(a);
-      copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, inl->pages[i], inl->slots[i], lane);
+      copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, inl->pages[i], inl->slots[i], lane,
+                                  0, a.piece_bytes >> 4);
       yield_link(a, busy, debt);
     }
   } else {
@@ -181,12 +181,37 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
         const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)vslot >> 32), k);
         const uint32_t busy = link_busy(a);
         copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, page,
-                                    (int64_t)(((uint64_t)hi << 32) | lo), lane);
+                                    (int64_t)(((uint64_t)hi << 32) | lo), lane, 0,
+                                    a.piece_bytes >> 4);
         yield_link(a, busy, debt);
       }
     }
   }
   mark_load(a, lane, -1);
+}
+
+// HBM copies whose pieces are cut into parts (slot of entry i is i / C):
+// part p of unit u is work item (u << part_shift) + p, one wave per item,
+// page ids read as scalars from the kernel arguments.  A wave has 4 KiB in
+// flight, so 8 pages of 32 layers x 64 KiB as 256 whole pieces kept 1 MiB in
+// flight and took 16 round trips (21 us); as 4,096 parts all of it is in
+// flight at once (8 us or less, the host's time per call).
+template <int DIR, int VEC>
+__device__ __forceinline__ void piece_parts(const PieceCopy &a, const int32_t *pages) {
+  const uint32_t items = (uint32_t)(a.n * a.layer_count) << a.part_shift;
+  const uint32_t waves = gridDim.x * (kThreads / kWave);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t nvec = a.piece_bytes >> 4;
+  for (uint32_t w = blockIdx.x * (kThreads / kWave) +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+       w < items; w += waves) {
+    const uint32_t u = w >> a.part_shift;
+    const int64_t v0 = (int64_t)(w - (u << a.part_shift)) * a.part_vecs;
+    const int64_t v1 = v0 + a.part_vecs < nvec ? v0 + a.part_vecs : nvec;
+    const uint32_t i = u / (uint32_t)a.layer_count;
+    copy_unit<DIR, false, VEC>(a, a.layer_begin + (u - i * a.layer_count), i, pages[i],
+                               i / (uint32_t)a.chunk, lane, v0, v1);
+  }
 }
 
 // Two entry points with the same body, so that profiles tell the host-link
@@ -202,6 +227,7 @@ template <int DIR, bool INLINE, int VEC>
 __global__ __launch_bounds__(kThreads) void copy_hbm(PieceCopy a, const int32_t *__restrict__ pages,
                                                      const int64_t *__restrict__ slot_idx,
                                                      InlineIdx inl) {
+  if (INLINE && a.part_shift > 0) return piece_parts<DIR, VEC>(a, inl.pages);
   piece_copy<DIR, INLINE, VEC>(a, pages, slot_idx, &inl);
 }
 // The HBM gather/scatter with the page ids of up to kArgPagesMax entries in
@@ -210,6 +236,7 @@ __global__ __launch_bounds__(kThreads) void copy_hbm(PieceCopy a, const int32_t 
 // the host would have to track.
 template <int DIR, int VEC>
 __global__ __launch_bounds__(kThreads) void copy_hbm_args(PieceCopy a, ArgPages ids) {
+  if (a.part_shift > 0) return piece_parts<DIR, VEC>(a, ids.pages);
   piece_copy<DIR, false, VEC>(a, ids.pages, nullptr, nullptr);
 }
 
@@ -337,6 +364,11 @@ hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const Arg
                              int dir, int route, int64_t workgroups, hipStream_t stream) {
   const int64_t units = a.n * a.layer_count;
   if (units <= 0) return hipSuccess;
+  // parts: 32-bit work items, page ids in the arguments
+  if (a.part_shift < 0 || a.part_shift > 30 ||
+      (a.part_shift > 0 && ((units << a.part_shift) > INT32_MAX || a.part_vecs < 1 ||
+                            route != kRouteHbm || (inl == nullptr && ids == nullptr))))
+    return hipErrorInvalidValue;
   if (a.num_xcd < 1 || a.num_xcd > 32 || a.xcd_mask == 0 ||
       (a.num_xcd < 32 && (a.xcd_mask >> a.num_xcd) != 0))
     return hipErrorInvalidValue;
@@ -347,7 +379,7 @@ hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const Arg
                          a.n > kArgPagesMax))
     return hipErrorInvalidValue;
   const int64_t waves_per_group = kThreads / kWave;
-  const int64_t needed = (units + waves_per_group - 1) / waves_per_group;
+  const int64_t needed = ((units << a.part_shift) + waves_per_group - 1) / waves_per_group;
   const int64_t work = needed < workgroups ? needed : workgroups;
   const int64_t active = __builtin_popcount(a.xcd_mask);
   // each run of num_xcd consecutive workgroups holds `active` working ones

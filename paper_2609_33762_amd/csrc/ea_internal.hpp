@@ -41,6 +41,11 @@ struct PieceCopy {
   int32_t layer_count;
   int32_t identity_slots;    // slot of entry i is i / C (staging buffers)
   int32_t layer_major;       // units ordered layer by layer, else entry by entry
+  // HBM copies with identity slots whose units are too few to fill the chip:
+  // each unit is cut into 1 << part_shift parts of part_vecs 16-byte vectors
+  // (the last ones shorter or empty).  0: whole units.
+  int32_t part_shift;
+  int32_t part_vecs;
   // Loads first on the host link.  link_flag is the tier's count of load
   // waves at work (nullptr: no priority).  A load (link_role 2) raises it
   // by one per wave for the wave's whole loop; a store (link_role 1) that

@@ -294,6 +294,38 @@ def test_any_xcd_masks_copy_every_piece(masks, placement, monkeypatch):
     p.close()
 
 
+@pytest.mark.parametrize("head_dim,layers,n", [
+    (63, 3, 40),      # 4,032-byte pieces: whole, the largest that are
+    (64, 3, 1), (65, 3, 33),   # 4,096 whole; 4,160: two parts of 3 and 2 KiB
+    (129, 2, 32), (129, 2, 2048),  # 8,256: four parts of 3 KiB, the last empty
+    (1023, 2, 5), (1025, 2, 900),  # beside 64 KiB; 65,600 past 112 MiB: 13-KiB parts
+    (1024, 2, 897), (1024, 2, 895),  # just past 112 MiB and just below
+])
+@pytest.mark.parametrize("scales", [False, True])
+def test_gather_and_scatter_of_cut_pieces(head_dim, layers, n, scales):
+    # HBM copies cut pieces into parts by size; every byte, the scale words
+    # (taken by a piece's first part) and the slot trailers, full images
+    torch = need_gpu()
+    P = 2 * n + 3
+    p = Pair(P, layers, 16, 1, head_dim, 2, 1, scales=scales, seed=70 + head_dim)
+    r = W.rng(71 + n)
+    src = W.distinct(r, P, n)
+    dst = W.distinct(r, P, n, exclude=src)
+    slot = p.sizes["slot"]
+    buf = torch.full((n * slot + 64,), 0x5A, dtype=torch.uint8, device="cuda")
+    p.cache.gather(src, buf)
+    p.cache.scatter(buf, dst)
+    want = np.full((n, slot), 0x5A, np.uint8)
+    oracle.store_blocks(p.oshape, p.o_cache, p.o_sc, want, src, np.arange(n))
+    oracle.load_blocks(p.oshape, want, p.o_cache, p.o_sc, np.arange(n), dst)
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[:n * slot].reshape(n, slot), want)
+    assert (got[n * slot:] == 0x5A).all()
+    p.assert_equal("scatter")
+    p.close()
+
+
 @pytest.mark.parametrize("hbm_index", [None, "ring"])
 @pytest.mark.parametrize("placement", ["hardware", "index"])
 def test_one_workgroup_runs_many_index_batches(placement, hbm_index, monkeypatch):
