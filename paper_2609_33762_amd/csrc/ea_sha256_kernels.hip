@@ -1020,6 +1020,86 @@ __global__ __launch_bounds__(kScanThreads) void hash_offsets_write(
   }
 }
 
+// The same in one launch for batches of up to 16 x THREADS sequences, with no
+// scan state: workgroup b owns sequences b * THREADS .., one per thread, and
+// reads the offsets of the whole batch to sum what comes before it and to
+// check them all, rather than wait for the other workgroups.  Every launch of
+// a small batch is latency (5.6 us for hash_offsets_partials, 5.5 for
+// hash_offsets_write, at any size up to 16,384 sequences), and at most 128
+// KiB of offsets per workgroup come from L2 in less than the second one
+// takes.  Whole calls with both scans, 4 keys per sequence: 64 sequences 22.6
+// -> 20.0 us, 4,000 30.3 -> 22.4, 12,000 32.0 -> 27.2; past 16,384 the two
+// kernels stay (16,385 sequences of 2 keys 27.6 -> 26.4 with them).
+constexpr int kOneTiles = 16;
+constexpr int kOneSmall = 256, kOneLarge = 1024;  // THREADS
+
+template <typename Off, int THREADS, int TILES>
+__global__ __launch_bounds__(THREADS) void hash_offsets_one(
+    const int64_t *__restrict__ seq_off, int32_t n_seqs, int64_t n_tokens, int32_t block_tokens,
+    int32_t shift, int64_t keys_cap, int64_t *__restrict__ key_off_out, Off *__restrict__ koff,
+    Off *__restrict__ toff) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ int64_t lds[3 * kWaves];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int tiles = (n_seqs + THREADS - 1) / THREADS;
+  int64_t a[TILES], e[TILES];
+#pragma unroll
+  for (int j = 0; j < TILES; ++j) {
+    const int32_t s = j * THREADS + t;
+    a[j] = j < tiles && s < n_seqs ? seq_off[s] : 0;
+    e[j] = j < tiles && s < n_seqs ? seq_off[s + 1] : 0;
+  }
+  // an empty batch has one offset, which is checked too
+  const int64_t first = seq_off[0];
+  bool ok = first >= 0 && first <= n_tokens;
+  int64_t before = 0, total = 0, own = 0, own_a = 0;
+#pragma unroll
+  for (int j = 0; j < TILES; ++j) {
+    ok = ok && e[j] >= a[j] && e[j] <= n_tokens;
+    const int64_t c = ok ? full_blocks(e[j] - a[j], block_tokens, shift) : 0;
+    total += c;
+    before += j < (int)blockIdx.x ? c : 0;
+    own = j == (int)blockIdx.x ? c : own;
+    own_a = j == (int)blockIdx.x ? a[j] : own_a;
+  }
+  const bool bad = __syncthreads_or(ok ? 0 : 1) != 0;
+  int64_t upto = own;  // inclusive scan of the owned counts in the wave
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int64_t v = __shfl_up(upto, (unsigned)d, 64);
+    if (lane >= d) upto += v;
+    before += __shfl_xor(before, d, 64);
+    total += __shfl_xor(total, d, 64);
+  }
+  if (lane == 63) {
+    lds[wave] = upto;
+    lds[kWaves + wave] = before;
+    lds[2 * kWaves + wave] = total;
+  }
+  __syncthreads();
+  int64_t at = upto - own;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    at += (w < wave ? lds[w] : 0) + lds[kWaves + w];
+    total += lds[2 * kWaves + w];
+  }
+  const bool failed = bad || total > keys_cap;
+  const int32_t s = (int32_t)blockIdx.x * THREADS + t;
+  if (s < n_seqs) {
+    koff[s] = failed ? (Off)0 : (Off)at;
+    if (!failed) {
+      key_off_out[s] = at;
+      toff[s] = (Off)own_a;
+    }
+  }
+  if (blockIdx.x == 0 && t == 0) {
+    koff[n_seqs] = failed ? (Off)0 : (Off)total;
+    if (failed) key_off_out[0] = -1;
+    else key_off_out[n_seqs] = total;
+  }
+}
+
 // Zero the scan's ticket counter (a fill kernel rather than a memset, so
 // that a captured graph replays it safely).
 __global__ __launch_bounds__(64) void hash_scan_reset(uint64_t *ticket) {
@@ -1337,11 +1417,44 @@ int block_shift(int32_t block_tokens) {
   return (block_tokens & (block_tokens - 1)) == 0 ? __builtin_ctz(block_tokens) : -1;
 }
 
+template <typename Off>
+static void launch_offsets_one(const int64_t *d_seq_offsets, int32_t n_seqs, int64_t n_tokens,
+                               int32_t block_tokens, int shift, int64_t keys_cap,
+                               int64_t *d_key_offsets_out, Off *d_koff, Off *d_toff,
+                               hipStream_t stream) {
+  const int threads = n_seqs <= kOneTiles * kOneSmall ? kOneSmall : kOneLarge;
+  const dim3 g((unsigned)std::max(1, (n_seqs + threads - 1) / threads));
+  if (n_seqs <= kOneSmall)
+    hipLaunchKernelGGL((hash_offsets_one<Off, kOneSmall, 1>), g, dim3(kOneSmall), 0, stream,
+                       d_seq_offsets, n_seqs, n_tokens, block_tokens, shift, keys_cap,
+                       d_key_offsets_out, d_koff, d_toff);
+  else if (threads == kOneSmall)
+    hipLaunchKernelGGL((hash_offsets_one<Off, kOneSmall, kOneTiles>), g, dim3(kOneSmall), 0, stream,
+                       d_seq_offsets, n_seqs, n_tokens, block_tokens, shift, keys_cap,
+                       d_key_offsets_out, d_koff, d_toff);
+  else
+    hipLaunchKernelGGL((hash_offsets_one<Off, kOneLarge, kOneTiles>), g, dim3(kOneLarge), 0, stream,
+                       d_seq_offsets, n_seqs, n_tokens, block_tokens, shift, keys_cap,
+                       d_key_offsets_out, d_koff, d_toff);
+}
+
 hipError_t launch_hash_key_offsets(const int64_t *d_seq_offsets, int32_t n_seqs,
                                    int64_t n_tokens, int32_t block_tokens, int64_t keys_cap,
                                    int64_t *d_key_offsets_out, bool wide, void *d_koff,
                                    void *d_toff, void *d_state, hipStream_t stream) {
   const int shift = block_shift(block_tokens);
+  if (n_seqs <= kOneTiles * kOneLarge) {
+    (void)hipGetLastError();  // report this launch's status only
+    if (wide)
+      launch_offsets_one(d_seq_offsets, n_seqs, n_tokens, block_tokens, shift, keys_cap,
+                         d_key_offsets_out, static_cast<int64_t *>(d_koff),
+                         static_cast<int64_t *>(d_toff), stream);
+    else
+      launch_offsets_one(d_seq_offsets, n_seqs, n_tokens, block_tokens, shift, keys_cap,
+                         d_key_offsets_out, static_cast<int32_t *>(d_koff),
+                         static_cast<int32_t *>(d_toff), stream);
+    return hipGetLastError();
+  }
   const int64_t groups = hash_scan_groups(n_seqs);
   const ScanState st = scan_state(d_state, groups);
   (void)hipGetLastError();  // report this launch's status only

@@ -308,6 +308,32 @@ def test_device_offsets_many_sequences_and_forms(monkeypatch):
         assert np.array_equal(out.cpu().numpy()[:len(okeys)], okeys), form
 
 
+@pytest.mark.parametrize("b", [16, 48])
+@pytest.mark.parametrize("n", [0, 1, 255, 256, 257, 4095, 4096, 4097, 16383, 16384, 16385])
+def test_device_offsets_at_the_scan_sizes(n, b):
+    # one workgroup per 256 or 1,024 sequences in one launch, two launches
+    # past 16,384: the edges of each, blocks that are no power of two; then
+    # the same batch with its last offset past the tokens, which must fail
+    # and write no key
+    torch = need_gpu()
+    r = W.rng(310 + n)
+    lengths = [int(x) for x in r.integers(0, 3 * b, size=n)]
+    okeys, okoffs, out, d_koffs = device_offsets_case(torch, lengths, b, 311 + n, True)
+    torch.cuda.synchronize()
+    assert np.array_equal(d_koffs.cpu().numpy(), okoffs)
+    assert np.array_equal(out.cpu().numpy()[:len(okeys)], okeys)
+    toks, offs = W.sequences(312, lengths)
+    for bad in ([len(toks) + 1], [-1]) if n else ([-1],):
+        wrong = offs.copy()
+        wrong[-1 if bad[0] > 0 else 0] = bad[0]
+        d_tok = torch.zeros(max(len(toks), 1), dtype=torch.int32, device="cuda")[:len(toks)]
+        keys = torch.full((max(len(okeys), 1), 32), 0xEE, dtype=torch.uint8, device="cuda")
+        koffs = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        api.hash_blocks_device_offsets(d_tok, torch.as_tensor(wrong, device="cuda"), b, keys, koffs)
+        torch.cuda.synchronize()
+        assert int(koffs[0]) == -1 and (keys.cpu().numpy() == 0xEE).all()
+
+
 def test_device_offsets_batch_workload_size():
     # the batch of the hash benchmark: 65,536 sequences of 256 tokens
     torch = need_gpu()
