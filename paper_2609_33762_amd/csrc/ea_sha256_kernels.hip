@@ -205,29 +205,43 @@ __global__ __launch_bounds__(256) void sha256_midstates(
 // rounds 43..63, the key into LDS; a barrier, after which the schedule
 // wave reads the key, stores the previous one and starts the next key's
 // words.  Each wave runs its own loop with the same four barriers per key.
-#define EA_RND(SH, S0, S1, S2, K, VI, VO, NW)                                                    \
+// One round in place: the new word takes S2's register, so the roles of the
+// three state registers move on by one (new s0 = S2, s1 = S0, s2 = S1), and
+// V becomes the next round's.
+#define EA_RND(SH, S0, S1, S2, K)                                                            \
   "v_alignbit_b32 %[r1], %[" S0 "], %[" S0 "], %[c1]\n\t"                                    \
   "v_alignbit_b32 %[r2], %[" S0 "], %[" S0 "], %[c2]\n\t"                                    \
   "v_alignbit_b32 %[r3], %[" S0 "], %[" S0 "], %[c3]\n\t"                                    \
   "v_bitop3_b32 %[x], %[" S0 "], %[" S2 "], %[m] bitop3:0x78\n\t"                            \
-  "v_bitop3_b32 %[F], %[x], %[" S1 "], %[" S2 "] bitop3:0xca\n\t"                            \
-  "v_bitop3_b32 %[S], %[r1], %[r2], %[r3] bitop3:0x96\n\t"                                   \
-  "v_add3_u32 %[G], %[S], %[F], %[" VI "]\n\t"                                               \
-  "v_add_u32_dpp %[P], %[" S2 "], %[" K "] row_shr:" SH " row_mask:0xf bank_mask:0xf "           \
+  "v_bitop3_b32 %[x], %[x], %[" S1 "], %[" S2 "] bitop3:0xca\n\t"                            \
+  "v_bitop3_b32 %[r1], %[r1], %[r2], %[r3] bitop3:0x96\n\t"                                  \
+  "v_add3_u32 %[r1], %[r1], %[x], %[V]\n\t"                                                  \
+  "v_add_u32_dpp %[P], %[" S2 "], %[" K "] row_shr:" SH " row_mask:0xf bank_mask:0xf "       \
   "bound_ctrl:1\n\t"                                                                         \
-  "v_xad_u32 %[" VO "], %[" S2 "], %[m], %[P]\n\t"                                           \
-  "v_add_u32_dpp %[" NW "], %[G], %[G] row_shl:" SH " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-// The last round of a compression: no next V, two wait states instead.
-#define EA_RND_LAST(SH, S0, S1, S2, VI, NW)                                                      \
+  "v_xad_u32 %[V], %[" S2 "], %[m], %[P]\n\t"                                                \
+  "v_add_u32_dpp %[" S2 "], %[r1], %[r1] row_shl:" SH " row_mask:0xf bank_mask:0xf "         \
+  "bound_ctrl:1\n\t"
+// Three rounds bring the registers back to their roles.
+#define EA_RND3(SH, K0, K1, K2)                                                              \
+  EA_RND(SH, "s0", "s1", "s2", K0) EA_RND(SH, "s2", "s0", "s1", K1)                          \
+  EA_RND(SH, "s1", "s2", "s0", K2)
+// The last round of a compression: no next V, two wait states instead; s2
+// stays for the final sum.
+#define EA_RND_LAST(SH, S0, S1, S2, NW)                                                      \
   "v_alignbit_b32 %[r1], %[" S0 "], %[" S0 "], %[c1]\n\t"                                    \
   "v_alignbit_b32 %[r2], %[" S0 "], %[" S0 "], %[c2]\n\t"                                    \
   "v_alignbit_b32 %[r3], %[" S0 "], %[" S0 "], %[c3]\n\t"                                    \
   "v_bitop3_b32 %[x], %[" S0 "], %[" S2 "], %[m] bitop3:0x78\n\t"                            \
-  "v_bitop3_b32 %[F], %[x], %[" S1 "], %[" S2 "] bitop3:0xca\n\t"                            \
-  "v_bitop3_b32 %[S], %[r1], %[r2], %[r3] bitop3:0x96\n\t"                                   \
-  "v_add3_u32 %[G], %[S], %[F], %[" VI "]\n\t"                                               \
+  "v_bitop3_b32 %[x], %[x], %[" S1 "], %[" S2 "] bitop3:0xca\n\t"                            \
+  "v_bitop3_b32 %[r1], %[r1], %[r2], %[r3] bitop3:0x96\n\t"                                  \
+  "v_add3_u32 %[r1], %[r1], %[x], %[V]\n\t"                                                  \
   "s_nop 1\n\t"                                                                              \
-  "v_add_u32_dpp %[" NW "], %[G], %[G] row_shl:" SH " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+  "v_add_u32_dpp %[" NW "], %[r1], %[r1] row_shl:" SH " row_mask:0xf bank_mask:0xf "         \
+  "bound_ctrl:1\n\t"
+#define EA_TEMPS                                                                             \
+  [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x), [P] "=&v"(P)
+#define EA_STATE [s0] "+&v"(q.s0), [s1] "+&v"(q.s1), [s2] "+&v"(q.s2), [V] "+&v"(q.v)
+#define EA_LANE [c1] "v"(c.c1), [c2] "v"(c.c2), [c3] "v"(c.c3), [m] "v"(c.m)
 
 // Per-lane constants of the split round: rotation amounts and the side mask.
 struct SplitLane {
@@ -243,54 +257,55 @@ struct SplitState {
 // issue, and instructions that straddle a fetch boundary cost it (a lone
 // 3,500-key chain took 4.89 ms with the blocks where the code before them
 // left them, 4.62 aligned; 32 or 64 bytes cost more in padding than they
-// give: 5.17 and 5.75).
+// give: 5.17 and 5.75).  Between two blocks the compiler puts a wait state,
+// and with it the alignment another: blocks as long as the hand-over of the
+// words allows (four rounds each: 4.58 ms on that chain, up to twelve: 4.47).
 // The rounds in blocks, for a row shift of SH lanes between the sides:
-// NAME##4 four rounds (k0..k3 are K + W of the round after each, 1 on
-// a-lanes), NAME##3 three, NAME##_end rounds 62 and 63 (k0 of round 63).
+// NAME##n does n rounds (k: K + W of the round after each, 1 on a-lanes),
+// NAME##_end rounds 62 and 63 (k0 of round 63).
 #define EA_SPLIT_ROUNDS(NAME, SH)                                                            \
-  __device__ __forceinline__ void NAME##4(SplitState &q, uint32_t k0, uint32_t k1,           \
-                                          uint32_t k2, uint32_t k3, const SplitLane &c) {    \
-    uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, v2, vo, n0, n1, n2, n3;                      \
-    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
-                 EA_RND(SH, "n0", "s0", "s1", "k1", "v0", "v1", "n1")                        \
-                 EA_RND(SH, "n1", "n0", "s0", "k2", "v1", "v2", "n2")                        \
-                 EA_RND(SH, "n2", "n1", "n0", "k3", "v2", "Vo", "n3")                        \
-                 : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
-                   [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
-                   [v1] "=&v"(v1), [v2] "=&v"(v2), [Vo] "=&v"(vo), [n0] "=&v"(n0),           \
-                   [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3)                            \
-                 : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v),             \
-                   [k0] "v"(k0), [k1] "v"(k1), [k2] "v"(k2), [k3] "v"(k3), [c1] "v"(c.c1),   \
-                   [c2] "v"(c.c2), [c3] "v"(c.c3), [m] "v"(c.m));                            \
-    q.s0 = n3; q.s1 = n2; q.s2 = n1; q.s3 = n0; q.v = vo;                                    \
+  __device__ __forceinline__ void NAME##2(SplitState &q, uint32_t k0, uint32_t k1,           \
+                                          const SplitLane &c) {                              \
+    uint32_t r1, r2, r3, x, P;                                                               \
+    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0")                         \
+                 EA_RND(SH, "s2", "s0", "s1", "k1")                                          \
+                 : EA_TEMPS, EA_STATE : [k0] "v"(k0), [k1] "v"(k1), EA_LANE);                \
+    const uint32_t n = q.s1; /* the newest of the two */                                     \
+    q.s1 = q.s2; q.s2 = q.s0; q.s0 = n;                                                      \
   }                                                                                          \
   __device__ __forceinline__ void NAME##3(SplitState &q, uint32_t k0, uint32_t k1,           \
                                           uint32_t k2, const SplitLane &c) {                 \
-    uint32_t r1, r2, r3, x, F, S, G, P, v0, v1, vo, n0, n1, n2;                              \
-    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
-                 EA_RND(SH, "n0", "s0", "s1", "k1", "v0", "v1", "n1")                        \
-                 EA_RND(SH, "n1", "n0", "s0", "k2", "v1", "Vo", "n2")                        \
-                 : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
-                   [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
-                   [v1] "=&v"(v1), [Vo] "=&v"(vo), [n0] "=&v"(n0), [n1] "=&v"(n1),           \
-                   [n2] "=&v"(n2)                                                            \
-                 : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v),             \
-                   [k0] "v"(k0), [k1] "v"(k1), [k2] "v"(k2), [c1] "v"(c.c1),                 \
-                   [c2] "v"(c.c2), [c3] "v"(c.c3), [m] "v"(c.m));                            \
-    q.s3 = q.s0; q.s0 = n2; q.s1 = n1; q.s2 = n0; q.v = vo;                                  \
+    uint32_t r1, r2, r3, x, P;                                                               \
+    asm volatile(".p2align 3\n\t" EA_RND3(SH, "k0", "k1", "k2")                              \
+                 : EA_TEMPS, EA_STATE : [k0] "v"(k0), [k1] "v"(k1), [k2] "v"(k2), EA_LANE);  \
+  }                                                                                          \
+  __device__ __forceinline__ void NAME##4(SplitState &q, uint4 k, const SplitLane &c) {      \
+    uint32_t r1, r2, r3, x, P;                                                               \
+    asm volatile(".p2align 3\n\t" EA_RND3(SH, "k0", "k1", "k2")                              \
+                 EA_RND(SH, "s0", "s1", "s2", "k3")                                          \
+                 : EA_TEMPS, EA_STATE                                                        \
+                 : [k0] "v"(k.x), [k1] "v"(k.y), [k2] "v"(k.z), [k3] "v"(k.w), EA_LANE);     \
+    const uint32_t n = q.s2;                                                                 \
+    q.s2 = q.s1; q.s1 = q.s0; q.s0 = n;                                                      \
+  }                                                                                          \
+  __device__ __forceinline__ void NAME##12(SplitState &q, uint4 k, uint4 l, uint4 n,         \
+                                           const SplitLane &c) {                             \
+    uint32_t r1, r2, r3, x, P;                                                               \
+    asm volatile(".p2align 3\n\t" EA_RND3(SH, "k0", "k1", "k2")                              \
+                 EA_RND3(SH, "k3", "k4", "k5") EA_RND3(SH, "k6", "k7", "k8")                 \
+                 EA_RND3(SH, "k9", "k10", "k11")                                             \
+                 : EA_TEMPS, EA_STATE                                                        \
+                 : [k0] "v"(k.x), [k1] "v"(k.y), [k2] "v"(k.z), [k3] "v"(k.w),               \
+                   [k4] "v"(l.x), [k5] "v"(l.y), [k6] "v"(l.z), [k7] "v"(l.w),               \
+                   [k8] "v"(n.x), [k9] "v"(n.y), [k10] "v"(n.z), [k11] "v"(n.w), EA_LANE);   \
   }                                                                                          \
   __device__ __forceinline__ void NAME##_end(SplitState &q, uint32_t k0,                     \
                                              const SplitLane &c) {                           \
-    uint32_t r1, r2, r3, x, F, S, G, P, v0, n0, n1;                                          \
-    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0", "V", "v0", "n0")                         \
-                 EA_RND_LAST(SH, "n0", "s0", "s1", "v0", "n1")                               \
-                 : [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3), [x] "=&v"(x),             \
-                   [F] "=&v"(F), [S] "=&v"(S), [G] "=&v"(G), [P] "=&v"(P), [v0] "=&v"(v0),   \
-                   [n0] "=&v"(n0), [n1] "=&v"(n1)                                            \
-                 : [s0] "v"(q.s0), [s1] "v"(q.s1), [s2] "v"(q.s2), [V] "v"(q.v),             \
-                   [k0] "v"(k0), [c1] "v"(c.c1), [c2] "v"(c.c2), [c3] "v"(c.c3),             \
-                   [m] "v"(c.m));                                                            \
-    q.s3 = q.s1; q.s2 = q.s0; q.s1 = n0; q.s0 = n1;                                          \
+    uint32_t r1, r2, r3, x, P, n;                                                            \
+    asm volatile(".p2align 3\n\t" EA_RND(SH, "s0", "s1", "s2", "k0")                         \
+                 EA_RND_LAST(SH, "s2", "s0", "s1", "n")                                      \
+                 : EA_TEMPS, EA_STATE, [n] "=&v"(n) : [k0] "v"(k0), EA_LANE);                \
+    q.s3 = q.s1; q.s1 = q.s2; q.s2 = q.s0; q.s0 = n;                                         \
   }
 EA_SPLIT_ROUNDS(split_rounds, "12")
 EA_SPLIT_ROUNDS(pair_rounds, "8")
@@ -434,30 +449,24 @@ __global__ __launch_bounds__(128) void sha256_chain_split(
 #pragma unroll
       for (int t = 4; t < 8; ++t) kw[t] = e_lane ? o[t - 4] + kc[t] : 1u;
       q.v = (q.s3 ^ c.m) + (row_move<kRowShr12>(q.s3) + kw[0]);
-      split_rounds4(q, kw[1], kw[2], kw[3], kw[4], c);      // rounds 0..3
-      split_rounds4(q, kw[5], kw[6], kw[7], kwc[0], c);     // 4..7
-      split_rounds4(q, kwc[1], kwc[2], kwc[3], kwc[4], c);  // 8..11
+      split_rounds12(q, make_uint4(kw[1], kw[2], kw[3], kw[4]),
+                     make_uint4(kw[5], kw[6], kw[7], kwc[0]),
+                     make_uint4(kwc[1], kwc[2], kwc[3], kwc[4]), c);  // rounds 0..11
       __syncthreads();
       uint4 a0 = kw4[0], a1 = kw4[1], a2 = kw4[2], a3 = kw4[3];  // t = 16..31
-      split_rounds3(q, kwc[5], kwc[6], kwc[7], c);          // 12..14
-      split_rounds4(q, a0.x, a0.y, a0.z, a0.w, c);          // 15..18
-      split_rounds4(q, a1.x, a1.y, a1.z, a1.w, c);          // 19..22
-      split_rounds4(q, a2.x, a2.y, a2.z, a2.w, c);          // 23..26
+      split_rounds3(q, kwc[5], kwc[6], kwc[7], c);  // 12..14
+      split_rounds12(q, a0, a1, a2, c);             // 15..26
       __syncthreads();
-      a0 = kw4[4]; a1 = kw4[5]; a2 = kw4[6];                // t = 32..43
-      const uint4 b3 = kw4[7];                               // t = 44..47
-      split_rounds4(q, a3.x, a3.y, a3.z, a3.w, c);          // 27..30
-      split_rounds4(q, a0.x, a0.y, a0.z, a0.w, c);          // 31..34
-      split_rounds4(q, a1.x, a1.y, a1.z, a1.w, c);          // 35..38
-      split_rounds4(q, a2.x, a2.y, a2.z, a2.w, c);          // 39..42
+      a0 = kw4[4]; a1 = kw4[5]; a2 = kw4[6];        // t = 32..43
+      const uint4 b3 = kw4[7];                       // t = 44..47
+      split_rounds4(q, a3, c);                      // 27..30
+      split_rounds12(q, a0, a1, a2, c);             // 31..42
       __syncthreads();
       a0 = kw4[8]; a1 = kw4[9]; a2 = kw4[10]; a3 = kw4[11];  // t = 48..63
-      split_rounds4(q, b3.x, b3.y, b3.z, b3.w, c);          // 43..46
-      split_rounds4(q, a0.x, a0.y, a0.z, a0.w, c);          // 47..50
-      split_rounds4(q, a1.x, a1.y, a1.z, a1.w, c);          // 51..54
-      split_rounds4(q, a2.x, a2.y, a2.z, a2.w, c);          // 55..58
-      split_rounds3(q, a3.x, a3.y, a3.z, c);                // 59..61
-      split_rounds_end(q, a3.w, c);                         // 62, 63
+      split_rounds4(q, b3, c);                      // 43..46
+      split_rounds12(q, a0, a1, a2, c);             // 47..58
+      split_rounds3(q, a3.x, a3.y, a3.z, c);        // 59..61
+      split_rounds_end(q, a3.w, c);                 // 62, 63
       o[0] = h0.x + q.s0; o[1] = h0.y + q.s1; o[2] = h0.z + q.s2; o[3] = h0.w + q.s3;
       *key_dst = make_uint4(o[0], o[1], o[2], o[3]);
       __syncthreads();
@@ -609,9 +618,9 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
 #pragma unroll
       for (int t = 4; t < 8; ++t) kw[t] = e_lane ? o[t - 4] + kc[t] : 1u;
       q.v = (q.s3 ^ c.m) + (row_move<kRowShr8>(q.s3) + kw[0]);
-      pair_rounds4(q, kw[1], kw[2], kw[3], kw[4], c);      // rounds 0..3
-      pair_rounds4(q, kw[5], kw[6], kw[7], kwc[0], c);     // 4..7
-      pair_rounds4(q, kwc[1], kwc[2], kwc[3], kwc[4], c);  // 8..11
+      pair_rounds12(q, make_uint4(kw[1], kw[2], kw[3], kw[4]),
+                    make_uint4(kw[5], kw[6], kw[7], kwc[0]),
+                    make_uint4(kwc[1], kwc[2], kwc[3], kwc[4]), c);  // rounds 0..11
       __syncthreads();
       uint4 w = *b0;                                        // words 16..19
       pair_rounds3(q, kwc[5], kwc[6], kwc[7], c);          // 12..14
@@ -619,7 +628,7 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
       for (int p = 1; p < kPpParts; ++p) {
         __syncthreads();
         const uint4 wn = (p & 1) ? *b1 : *b0;
-        pair_rounds4(q, w.x, w.y, w.z, w.w, c);             // 11 + 4p .. 14 + 4p
+        pair_rounds4(q, w, c);                               // 11 + 4p .. 14 + 4p
         w = wn;
       }
       pair_rounds3(q, w.x, w.y, w.z, c);                    // 59..61
@@ -766,20 +775,18 @@ __global__ __launch_bounds__(128) void sha256_midstates_split(
     __syncthreads();  // block 0's words
     for (int32_t cb = 0; cb < blocks; ++cb) {
       const uint4 *kw4 = reinterpret_cast<const uint4 *>(lds + kbase + (cb & 1) * kstep);
-      uint32_t kw[64];
+      uint4 kw[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const uint4 v = kw4[i];
-        kw[4 * i] = v.x; kw[4 * i + 1] = v.y; kw[4 * i + 2] = v.z; kw[4 * i + 3] = v.w;
-      }
+      for (int i = 0; i < 16; ++i) kw[i] = kw4[i];
+      // the rounds take K + W one round ahead: words 4i + 1 .. 4i + 4
+      auto next4 = [&](int i) { return make_uint4(kw[i].y, kw[i].z, kw[i].w, kw[i + 1].x); };
       SplitState q{h0, h1, h2, h3, 0u};
-      q.v = (q.s3 ^ c.m) + (row_move<kRowShr12>(q.s3) + kw[0]);
+      q.v = (q.s3 ^ c.m) + (row_move<kRowShr12>(q.s3) + kw[0].x);
 #pragma unroll
-      for (int t = 0; t < 56; t += 4)  // rounds 0..55
-        split_rounds4(q, kw[t + 1], kw[t + 2], kw[t + 3], kw[t + 4], c);
-      split_rounds3(q, kw[57], kw[58], kw[59], c);  // 56..58
-      split_rounds3(q, kw[60], kw[61], kw[62], c);  // 59..61
-      split_rounds_end(q, kw[63], c);               // 62, 63
+      for (int i = 0; i < 15; i += 3)  // rounds 0..59
+        split_rounds12(q, next4(i), next4(i + 1), next4(i + 2), c);
+      split_rounds2(q, kw[15].y, kw[15].z, c);  // 60, 61
+      split_rounds_end(q, kw[15].w, c);         // 62, 63
       h0 += q.s0; h1 += q.s1; h2 += q.s2; h3 += q.s3;
       __syncthreads();
     }
