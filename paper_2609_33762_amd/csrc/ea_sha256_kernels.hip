@@ -441,7 +441,7 @@ __global__ __launch_bounds__(128) void sha256_chain_split(
     uint4 *key_dst = reinterpret_cast<uint4 *>(lds + kst);
     for (Off kk = 0; kk < kmax; ++kk) {
       const uint4 h0 = nx;
-      if (kk + 1 < kmax) nx = mid_at(kk + 1);
+      nx = mid_at(kk + 1);  // past the end: the last one again
       SplitState q{h0.x, h0.y, h0.z, h0.w, 0u};
       uint32_t kw[8];  // K + W of rounds 0..7: the previous key
 #pragma unroll
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
     const uint4 *b1 = reinterpret_cast<const uint4 *>(lds + at1);
     for (Off kk = 0; kk < kmax; ++kk) {
       const uint4 h0 = nx;
-      if (kk + 1 < kmax) nx = mid_at(kk + 1);
+      nx = mid_at(kk + 1);  // past the end: the last one again
       SplitState q{h0.x, h0.y, h0.z, h0.w, 0u};
       uint32_t kw[8];  // K + W of rounds 0..7: the previous key
 #pragma unroll
