@@ -55,12 +55,11 @@ struct HashWs {
   hipEvent_t done_dev = nullptr;
   hipEvent_t last = nullptr;
   bool used = false;
-  // ea_hash_blocks: pinned host staging
-  uint8_t *h_tok = nullptr;  int64_t cap_tok = 0;   // bytes
-  uint8_t *h_meta = nullptr; int64_t cap_meta = 0;  // offsets + parents
+  // ea_hash_blocks: pinned host staging and its device twins; offsets,
+  // parents and tokens travel together
+  uint8_t *h_in = nullptr;   int64_t cap_in = 0;    // bytes
   uint8_t *h_keys = nullptr; int64_t cap_keys = 0;  // bytes
-  uint8_t *d_tok = nullptr;
-  uint8_t *d_meta = nullptr;
+  uint8_t *d_in = nullptr;
   uint8_t *d_keys = nullptr;
   uint32_t *d_mid = nullptr; int64_t cap_mid = 0;   // keys
   DevSlot slots[2];                                 // ea_hash_blocks_device
@@ -153,6 +152,10 @@ int ensure_mid(HashWs &w, uint32_t **mid, int64_t *cap, int64_t keys) {
   *cap = c;
   return EA_OK;
 }
+
+// Keys of a host-keys call that the kernels store to pinned host memory
+// directly (128 KiB).
+constexpr int64_t kMappedKeys = 4096;
 
 // floor(len / b), the full blocks of a sequence: a shift when b is a power
 // of two (16-token pages, 1,024-token chunks), else a division.
@@ -269,29 +272,34 @@ extern "C" int ea_hash_blocks(const int32_t *tokens, const int64_t *seq_offsets,
   const int64_t tok_bytes = total * block_tokens * 4;
   const bool wide = total * block_tokens > INT32_MAX || force_wide();
   const int64_t off_bytes = offsets_bytes(n_seqs, wide);
-  const int64_t meta_bytes = off_bytes + (parents ? 32 * (int64_t)n_seqs : 0);
-  if ((rc = grow_pair(w, &w.h_tok, &w.d_tok, &w.cap_tok, tok_bytes)) != EA_OK) return rc;
-  if ((rc = grow_pair(w, &w.h_meta, &w.d_meta, &w.cap_meta, meta_bytes)) != EA_OK) return rc;
+  const int64_t tok_at = (off_bytes + (parents ? 32 * (int64_t)n_seqs : 0) + 255) / 256 * 256;
+  if ((rc = grow_pair(w, &w.h_in, &w.d_in, &w.cap_in, tok_at + tok_bytes)) != EA_OK) return rc;
   if ((rc = grow_pair(w, &w.h_keys, &w.d_keys, &w.cap_keys, total * 32)) != EA_OK) return rc;
   if ((rc = ensure_mid(w, &w.d_mid, &w.cap_mid, total)) != EA_OK) return rc;
 
   for (int32_t s = 0; s < n_seqs; ++s) {
     const int64_t nt = (key_offsets_out[s + 1] - key_offsets_out[s]) * block_tokens;
-    std::memcpy(w.h_tok + key_offsets_out[s] * block_tokens * 4, tokens + seq_offsets[s],
+    std::memcpy(w.h_in + tok_at + key_offsets_out[s] * block_tokens * 4, tokens + seq_offsets[s],
                 (size_t)nt * 4);
   }
-  put_offsets(w.h_meta, key_offsets_out, nullptr, block_tokens, n_seqs, wide);
-  if (parents) std::memcpy(w.h_meta + off_bytes, parents, (size_t)n_seqs * 32);
+  put_offsets(w.h_in, key_offsets_out, nullptr, block_tokens, n_seqs, wide);
+  if (parents) std::memcpy(w.h_in + off_bytes, parents, (size_t)n_seqs * 32);
 
-  HS_HIP(hipMemcpyAsync(w.d_tok, w.h_tok, (size_t)tok_bytes, hipMemcpyHostToDevice, stream));
-  HS_HIP(hipMemcpyAsync(w.d_meta, w.h_meta, (size_t)meta_bytes, hipMemcpyHostToDevice, stream));
-  const uint8_t *d_koff = w.d_meta;
+  // One copy in; every further one is about 5 us of an 80-us call for four
+  // short prompts.  Up to kMappedKeys keys the chain kernels store to the
+  // pinned buffer themselves instead of through a copy back.
+  HS_HIP(hipMemcpyAsync(w.d_in, w.h_in, (size_t)(tok_at + tok_bytes), hipMemcpyHostToDevice,
+                        stream));
+  const uint8_t *d_koff = w.d_in;
   const uint8_t *d_toff = d_koff + (n_seqs + 1) * (wide ? 8 : 4);
-  const uint8_t *d_par = parents ? w.d_meta + off_bytes : nullptr;
-  if ((rc = run_kernels(reinterpret_cast<const int32_t *>(w.d_tok), d_koff, d_toff, wide,
-                        n_seqs, total, block_tokens, w.d_mid, d_par, w.d_keys, stream)) != EA_OK)
+  const uint8_t *d_par = parents ? w.d_in + off_bytes : nullptr;
+  uint8_t *d_keys = w.d_keys;
+  if (total <= kMappedKeys) HS_HIP(hipHostGetDevicePointer((void **)&d_keys, w.h_keys, 0));
+  if ((rc = run_kernels(reinterpret_cast<const int32_t *>(w.d_in + tok_at), d_koff, d_toff, wide,
+                        n_seqs, total, block_tokens, w.d_mid, d_par, d_keys, stream)) != EA_OK)
     return rc;
-  HS_HIP(hipMemcpyAsync(w.h_keys, w.d_keys, (size_t)total * 32, hipMemcpyDeviceToHost, stream));
+  if (d_keys == w.d_keys)
+    HS_HIP(hipMemcpyAsync(w.h_keys, w.d_keys, (size_t)total * 32, hipMemcpyDeviceToHost, stream));
   if ((rc = release(w, stream, true)) != EA_OK) return rc;
   HS_HIP(hipEventSynchronize(w.done));  // this workspace's lock only
   std::memcpy(keys_out, w.h_keys, (size_t)total * 32);
