@@ -294,6 +294,32 @@ def test_any_xcd_masks_copy_every_piece(masks, placement, monkeypatch):
     p.close()
 
 
+@pytest.mark.parametrize("layers", [1, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("n", [3, 40])
+def test_scale_words_of_layer_groups(layers, n):
+    # every eighth layer's unit moves the scale words of eight layers: layer
+    # counts around the groups' ends, through store, load and layered load;
+    # full images (no other page's or slot's words move)
+    torch = need_gpu()
+    p = Pair(4 * n, layers, 16, 1, 32, 1, 2 * n, scales=True, seed=80 + layers, fp8=True)
+    r = W.rng(81 + n)
+    src = W.distinct(r, 4 * n, n)
+    slots = W.distinct(r, 2 * n, n)
+    dst = W.distinct(r, 4 * n, n, exclude=src)
+    dst2 = W.distinct(r, 4 * n, n, exclude=np.concatenate([src, dst]))
+    p.tier.store(p.cache, src, slots)
+    p.o_store(src, slots)
+    p.assert_equal("store")
+    p.tier.load(p.cache, slots, dst)
+    p.o_load(slots, dst)
+    p.assert_equal("load")
+    events = [torch.cuda.Event() for _ in range(layers)]
+    p.tier.load_layered(p.cache, slots, dst2, torch.cuda.Stream(), events)
+    p.o_load(slots, dst2)
+    p.assert_equal("layered load")
+    p.close()
+
+
 @pytest.mark.parametrize("head_dim,layers,n", [
     (63, 3, 40),      # 4,032-byte pieces: whole, the largest that are
     (64, 3, 1), (65, 3, 33),   # 4,096 whole; 4,160: two parts of 3 and 2 KiB
