@@ -132,6 +132,22 @@ def test_every_chain_form(form, monkeypatch):
 
 
 @pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("n", [1, 64, 512, 513, 4096, 4097, 9000])
+def test_owners_of_a_wave_of_keys(n, wide, monkeypatch):
+    # past 512 sequences a wave finds the owners of its 64 keys together: batch
+    # sizes around that and the steps of 64, ragged and one-key sequences
+    # (64 owners) and mostly empty ones (more than 64 sequences start inside
+    # one wave's keys), the last ones empty
+    if wide:
+        monkeypatch.setenv("EA_HASH_OFFSETS", "64")
+    r = W.rng(320 + n)
+    check([16 * int(k) for k in r.integers(0, 4, size=n)], 16, seed=321 + n)
+    check([16] * n, 16, parents=True, seed=322 + n)
+    sparse = [16 * int(k) if r.random() < 0.02 else 3 for k in r.integers(1, 90, size=n)]
+    check(sparse + [16 * 130] + [0] * 70, 16, seed=323 + n)
+
+
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("n", [1, 8, 31, 32, 33, 63, 64, 65, 200])
 def test_two_lane_form_at_its_workgroup_edges(n, wide, monkeypatch):
     # 64 chains per workgroup, 32 per pair of waves, 8 per row: part-filled
