@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void sha256_midstates(
 // e-lane and ~A_t-3 on the a-lane (~x + 1 = -x).  Ten instructions per
 // round, no wait states, and every VGPR a DPP instruction reads was
 // written at least two instructions before it.  The rounds sit in asm
-// blocks of up to four (the compiler adds a wait state between blocks);
+// blocks of up to twelve (the compiler adds a wait state between blocks);
 // volatile keeps them where they are written relative to the barriers.
 //
 // Schedule wave.  Lane j of a row holds W_T0-16+j and computes W_T0+j for
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(128) void sha256_chain_split(
 // instructions per key as in the row form, while a wave carries eight times
 // as many chains.  With the rounds and the schedule in one wave (1,150
 // instructions per key, the form before this one) 12,000 ragged chains of up
-// to 125 keys took 322 us of chain kernel, here 203.  Four waves
+// to 125 keys took 322 us of chain kernel, here 180.  Four waves
 // per workgroup rather than two, because a CU puts the second wave of one
 // two-wave workgroup and the first of the next on one SIMD and leaves
 // another empty (read from HW_REG_HW_ID): 16,384 chains of 256 keys took
