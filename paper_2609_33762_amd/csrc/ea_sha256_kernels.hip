@@ -589,7 +589,8 @@ constexpr int kPpThreads = 256;
 constexpr int kPpParts = 12;
 constexpr int kPpBuf = 4 * kPpChains;  // 32-bit words of one buffer
 constexpr int kPpOnes = 2 * kPpBuf;    // four ones: the a-lanes' K + W
-constexpr int kPpWords = kPpOnes + 4;
+constexpr int kPpLongest = kPpOnes + 4;  // the longest chain of each pair (two Off)
+constexpr int kPpWords = kPpLongest + 4;
 
 template <typename Off>
 __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
@@ -606,8 +607,8 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
     k0 = key_off[s];
     k1 = key_off[s + 1];
   }
-  // Both waves run the longest chain's number of keys, so they meet at the
-  // same barriers; a chain past its end computes keys that are never stored.
+  // Both waves of a pair run the longest of the pair's chains; a chain past
+  // its end computes keys that are never stored.
   const Off len = (Off)(k1 - k0);
   Off kmax = len;
 #pragma unroll
@@ -622,10 +623,18 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
     const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)kmax >> 32));
     kmax = (Off)(((uint64_t)hi << 32) | lo);
   }
+  // A barrier is the whole workgroup's, and the pairs' longest chains differ:
+  // the pair that is done first meets the other's barriers (kPpParts + 1 a
+  // key) below.  That number and the ones are in LDS before any wave parts.
+  // 12,000 ragged chains take 225 us per call with it and without it.
+  Off *longest = reinterpret_cast<Off *>(lds + kPpLongest);
+  if (threadIdx.x < 4) lds[kPpOnes + threadIdx.x] = 1u;
+  if ((wave & 1) == 0 && lane == 0) longest[wave >> 1] = kmax;
+  __syncthreads();
+  const Off other = longest[1 - (wave >> 1)];
   const uint8_t *par = s < n_seqs ? parents : nullptr;
   uint4 *slot = reinterpret_cast<uint4 *>(lds) + chain;  // of buffer 0; buffer 1: + kPpChains
   if ((wave & 1) == 0) {
-    if (wave == 0 && lane < 4) lds[kPpOnes + lane] = 1u;
     SplitLane c;
     c.c1 = e_lane ? 6 : 2;
     c.c2 = e_lane ? 11 : 13;
@@ -739,6 +748,10 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
       *reinterpret_cast<uint4 *>(keys + 32 * (k1 - 1) + (e_lane ? 16 : 0)) =
           make_uint4(__builtin_bswap32(half[0]), __builtin_bswap32(half[1]),
                      __builtin_bswap32(half[2]), __builtin_bswap32(half[3]));
+  }
+  for (Off kk = kmax; kk < other; ++kk) {
+#pragma unroll
+    for (int p = 0; p <= kPpParts; ++p) __syncthreads();
   }
 }
 

@@ -166,6 +166,22 @@ def test_two_lane_form_at_its_workgroup_edges(n, wide, monkeypatch):
         check([0] * at + [16 * 9] + [0] * (n - 1 - at), 16, parents=True, seed=302 + n)
 
 
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("first,second", [(0, 9), (9, 0), (1, 60), (60, 1), (0, 0), (7, 7)])
+def test_two_lane_pairs_of_unequal_length(first, second, wide, monkeypatch):
+    # the longest chains of a workgroup's two pairs of waves: one pair without
+    # a key, or done long before the other, in a workgroup alone and among
+    # others, with parents
+    monkeypatch.setenv("EA_HASH_CHAIN", "pair")
+    if wide:
+        monkeypatch.setenv("EA_HASH_OFFSETS", "64")
+    r = W.rng(330 + first)
+    two = [16 * int(r.integers(0, m + 1)) for m in (first, second) for _ in range(32)]
+    two[5], two[40] = 16 * first, 16 * second
+    check(two, 16, parents=True, seed=331 + second)
+    check(two + [16 * 20] * 64 + two[32:] + two[:32] + two[:3], 16, parents=True, seed=332)
+
+
 def test_batch_past_the_one_lane_threshold():
     # more sequences than two-lane waves fit one per SIMD (32 per SIMD):
     # the library picks the one-lane chain by itself; ragged lengths, parents;

@@ -205,3 +205,29 @@ def test_asm_dpp_reads_keep_their_wait_states(assembly):
         bad = _dpp_hazards(instrs)
         assert not bad, (name, bad[:3])
     assert checked > 0, "no DPP instruction inside asm found"
+
+
+# ------------------------------------------------------------------ barriers
+def test_two_lane_chain_waves_share_one_start_and_one_barrier_count(assembly):
+    # The workgroup carries two pairs of waves whose longest chains differ.
+    # What the pairs share in LDS is written, and waited for, before the waves
+    # part into their roles (the schedule waves raise their priority, the
+    # rounds waves rotate); a pair whose keys end first meets the other's
+    # barriers with nothing between them.
+    bodies, _, _ = kernels(assembly["ea_sha256_kernels.hip"])
+    pair = {n: b for n, b in bodies.items() if "sha256_chain_pair_split" in n}
+    assert len(pair) == 2, sorted(pair)  # 32- and 64-bit offsets
+    for name, body in pair.items():
+        ops = [op for op, _, _ in _instructions(body)]
+        before = ops[:ops.index("s_barrier")]
+        assert any(op.startswith("ds_write") for op in before), name
+        assert "s_setprio" not in before and "v_alignbit_b32" not in before, name
+        # 13 barriers a key in either role, and 13 that stand alone
+        run = best = 0
+        for op in ops:
+            if op == "s_barrier":
+                run += 1
+                best = max(best, run)
+            elif op not in ("s_waitcnt", "s_nop"):
+                run = 0
+        assert best >= 13, (name, best)
