@@ -504,7 +504,9 @@ int ea_load_blocks(ea_tier *tier, ea_cache *cache, const int64_t *host_slots,
  * the library records layer_done[l] (caller-created events; n_events must
  * equal the cache's num_layers, else EA_EINVAL), so a consumer stream can
  * hipStreamWaitEvent(layer_done[l]) and use layer l of every destination
- * page while later layers are still in flight. */
+ * page while later layers are still in flight.  Calls of more than 32 pages
+ * pass their indices through device memory that the tier keeps (48 bytes per
+ * page of the largest load), or without it where the device is full. */
 int ea_load_blocks_layered(ea_tier *tier, ea_cache *cache,
                            const int64_t *host_slots, const int32_t *dst_pages,
                            int32_t n, hipStream_t copy_stream,

@@ -235,7 +235,9 @@ bool all_distinct(const T *v, int64_t n) {
 // regions: the host writes region r and the kernels read it in place over
 // the link (one 64-entry vector load per wave per 64 units), with no DMA
 // and no device copy.  That measured 1-2% faster on MI355X than uploading
-// each call's indices into a device twin first.  Region r is rewritten only
+// each call's indices into a device twin first; only a layered load, whose
+// kernels each read the same indices, makes a device copy (to_device).
+// Region r is rewritten only
 // after the event recorded behind its last consumer has fired, so
 // back-to-back calls never wait on each other unless kRegions calls are
 // still in flight.  The events only tell the host that the kernels have
@@ -260,18 +262,19 @@ class IndexRing {
     return EA_OK;
   }
 
-  // Copy region r's arrays of n entries into device memory on stream s, ahead
-  // of consumers that read them many times, and point at that copy.  It
-  // lives as long as the region.
-  int to_device(int r, int64_t n, bool slots, const int64_t **d_slots, const int32_t **d_pages,
+  // Keep device twins of the regions from now on, for to_device.
+  void keep_twins() { want_twins_ = true; }
+
+  // Copy region r's arrays of n entries into its device twin on stream s,
+  // ahead of consumers that read them many times, and point at that copy.
+  // Without device memory for the twins the consumers read the region itself.
+  int to_device(int r, int64_t n, const int64_t **d_slots, const int32_t **d_pages,
                 hipStream_t s) {
-    for (int k = 0; k < kRegions; ++k)  // all at once: no later call allocates
-      if (!twin_[k]) EA_HIP(hipMalloc((void **)&twin_[k], (size_t)cap_ * 12));
-    const int64_t first = slots ? 0 : n * 8;
-    EA_HIP(hipMemcpyAsync(twin_[r] + first, h_[r] + first, (size_t)(n * 12 - first),
-                          hipMemcpyHostToDevice, s));
-    if (slots) *d_slots = reinterpret_cast<const int64_t *>(twin_[r]);
-    *d_pages = reinterpret_cast<const int32_t *>(twin_[r] + n * 8);
+    if (!twins_) return EA_OK;
+    uint8_t *twin = twins_ + r * cap_ * 12;
+    EA_HIP(hipMemcpyAsync(twin, h_[r], (size_t)n * 12, hipMemcpyHostToDevice, s));
+    *d_slots = reinterpret_cast<const int64_t *>(twin);
+    *d_pages = reinterpret_cast<const int32_t *>(twin + n * 8);
     return EA_OK;
   }
 
@@ -289,24 +292,29 @@ class IndexRing {
         (void)hipEventDestroy(ev_[r]);
       }
       if (h_[r]) (void)hipHostFree(h_[r]);
-      if (twin_[r]) (void)hipFree(twin_[r]);
       ev_[r] = nullptr;
-      h_[r] = d_[r] = twin_[r] = nullptr;
+      h_[r] = d_[r] = nullptr;
       used_[r] = false;
     }
+    free_twins();
     cap_ = 0;
   }
 
  private:
+  void free_twins() {
+    if (twins_) (void)hipFree(twins_);
+    twins_ = nullptr;
+  }
+
   int reserve(int64_t n) {
     if (n <= cap_) return EA_OK;
     for (int r = 0; r < kRegions; ++r) {
       if (used_[r]) EA_HIP(hipEventSynchronize(ev_[r]));
       if (h_[r]) (void)hipHostFree(h_[r]);
-      if (twin_[r]) (void)hipFree(twin_[r]);
-      h_[r] = d_[r] = twin_[r] = nullptr;
+      h_[r] = d_[r] = nullptr;
       used_[r] = false;
     }
+    free_twins();
     cap_ = 0;
     const int64_t cap = std::max<int64_t>(n, 4096);
     for (int r = 0; r < kRegions; ++r) {
@@ -315,14 +323,23 @@ class IndexRing {
       EA_HIP(hipHostGetDevicePointer((void **)&d_[r], h_[r], 0));
       if (!ev_[r]) EA_HIP(hipEventCreateWithFlags(&ev_[r], ea::kDeviceEventFlags));
     }
+    // With the regions, so that a call that finds the ring large enough
+    // allocates nothing (it may be captured into a graph).  A full device is
+    // no error: the regions serve alone.
+    if (want_twins_ &&
+        hipMalloc((void **)&twins_, (size_t)(kRegions * cap * 12)) != hipSuccess) {
+      twins_ = nullptr;
+      (void)hipGetLastError();  // the caller's next check must not find it
+    }
     cap_ = cap;
     return EA_OK;
   }
 
   int64_t cap_ = 0;
+  bool want_twins_ = false;
   uint8_t *h_[kRegions] = {};
   uint8_t *d_[kRegions] = {};
-  uint8_t *twin_[kRegions] = {};  // device copy of the region, where one was asked for
+  uint8_t *twins_ = nullptr;      // device copies of the regions, cap_ * 12 bytes each
   hipEvent_t ev_[kRegions] = {};  // last consumer of the region done
   bool used_[kRegions] = {};
   int next_ = 0;
@@ -798,6 +815,7 @@ int ea_tier_create_chunked(const ea_cache *shape, int32_t chunk_pages, int64_t c
     const int nx = t->num_xcd;
     t->xcd_store = xcd_mask_from_env("EA_XCD_STORE", nx >= 4 ? 0x5u : 0x1u, nx);
     t->xcd_load = xcd_mask_from_env("EA_XCD_LOAD", nx >= 4 ? 0xAu : (nx > 1 ? 0x2u : 0x1u), nx);
+    t->res[EA_DIR_LOAD].ring.keep_twins();  // for layered loads
     t->grid_gather = grid_hbm(ea::kToSlots);
     t->grid_scatter = grid_hbm(ea::kToPages);
     // a layered load is one short kernel per layer: 16 workgroups hide the
@@ -1144,7 +1162,7 @@ int ea_load_blocks_layered(ea_tier *t, ea_cache *c, const int64_t *host_slots,
       // the link before its first piece.  48 layers of 4 KiB pieces, us a
       // layer: 40 pages 10.9 -> 9.7, 128 18.4 -> 16.7, 4,096 302.0 -> 300.4.
       EA_TRY(ring.upload(each.data(), dst_pages, m, &a.slot_idx, &a.pages, &region));
-      EA_TRY(ring.to_device(region, m, true, &a.slot_idx, &a.pages, copy_stream));
+      EA_TRY(ring.to_device(region, m, &a.slot_idx, &a.pages, copy_stream));
     }
     if (t->d_busy != nullptr) {
       a.link_flag = t->d_busy;

@@ -13,6 +13,10 @@ The oracle's hashing and copies also run on random ragged inputs (keys only
 for full blocks; store then load reproduces pages and scales).  Planted
 mistakes in a scratch copy of the tier (trimming one clock unit too much, a
 hit not promoted) are caught by these seeds.
+
+tests/sanitize/layered_indices.cpp runs the host side of the layered load on
+a stand-in for the HIP runtime whose device memory can run out: the call then
+works as it does with it.
 """
 import os
 import shutil
@@ -67,3 +71,20 @@ def test_random_streams_match_the_oracle_under_sanitizers(fuzz_binary, seed):
 
 def test_long_stream_with_bounded_history_under_sanitizers(fuzz_binary):
     run(fuzz_binary, 99, 80_000)
+
+
+def test_layered_load_with_and_without_device_memory_for_its_indices(tmp_path):
+    if not shutil.which("g++"):
+        pytest.skip("g++ not available")
+    if not os.path.exists(os.path.join(HIP_INCLUDE, "hip", "hip_runtime_api.h")):
+        pytest.skip("HIP headers not available")
+    exe = str(tmp_path / "layered_indices")
+    subprocess.run(["g++", "-std=c++17"] + FLAGS +
+                   ["-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
+                    "-I", HIP_INCLUDE, "-I", CSRC,
+                    os.path.join(ROOT, "tests", "sanitize", "layered_indices.cpp"),
+                    os.path.join(CSRC, "ea_api.cpp"), os.path.join(CSRC, "ea_tier_meta.cpp"),
+                    "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
+    assert "runtime error" not in r.stderr, r.stderr
