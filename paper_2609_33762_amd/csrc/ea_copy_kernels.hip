@@ -138,7 +138,8 @@ __device__ __forceinline__ void mark_load(const PieceCopy &a, int lane, int32_t 
                            __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int DIR, bool INLINE, int VEC>
+// LINK: a copy over the host link, with the priority above.
+template <int DIR, bool INLINE, int VEC, bool LINK>
 __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__restrict__ pages,
                                            const int64_t *__restrict__ slot_idx,
                                            const InlineIdx *inl) {
@@ -154,15 +155,15 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
   const int64_t first =
       group * (kThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   int64_t debt = 0;  // bytes a yielding store has copied since its last sleep
-  mark_load(a, lane, 1);
+  if (LINK) mark_load(a, lane, 1);
   if constexpr (INLINE) {
     // indices from the kernel arguments (scalar loads, u is wave-uniform)
     for (int64_t u = first; u < units; u += waves) {
       const int64_t i = unit_entry(a, u);
-      const uint32_t busy = link_busy(a);
+      const uint32_t busy = LINK ? link_busy(a) : 0;
       copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, inl->pages[i], inl->slots[i], lane,
                                   0, a.piece_bytes >> 4);
-      yield_link(a, busy, debt);
+      if (LINK) yield_link(a, busy, debt);
     }
   } else {
     // The index arrays live in pinned host memory that the kernel reads
@@ -188,15 +189,15 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
         const int64_t page = __builtin_amdgcn_readlane(vpage, k);
         const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)vslot, k);
         const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)vslot >> 32), k);
-        const uint32_t busy = link_busy(a);
+        const uint32_t busy = LINK ? link_busy(a) : 0;
         copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, page,
                                     (int64_t)(((uint64_t)hi << 32) | lo), lane, 0,
                                     a.piece_bytes >> 4);
-        yield_link(a, busy, debt);
+        if (LINK) yield_link(a, busy, debt);
       }
     }
   }
-  mark_load(a, lane, -1);
+  if (LINK) mark_load(a, lane, -1);
 }
 
 // HBM copies whose pieces are cut into parts (slot of entry i is i / C):
@@ -223,21 +224,29 @@ __device__ __forceinline__ void piece_parts(const PieceCopy &a, const int32_t *p
   }
 }
 
-// Two entry points with the same body, so that profiles tell the host-link
-// transfers (direct store/load, few workgroups) from the HBM gather/scatter.
+// Two entry points, so that profiles tell the host-link transfers (direct
+// store/load, few workgroups) from the HBM gather/scatter.  The HBM ones leave
+// out the link's priority, and only the four-vector ones hold the path for
+// parts (cut pieces are longer than one round of it): with everything in
+// every kernel up to seven scalar registers spill to lanes of a vector
+// register, and gathers of many whole pieces lose 1-2% (1,253 pages of 32 x 3
+// KiB 53.5 us, without 52.6; 1,706 pages 70.6 and 69.4; 2,000 of 32 x 8 KiB
+// 183.9 and 183.3).
 template <int DIR, bool INLINE, int VEC>
 __global__ __launch_bounds__(kThreads) void copy_host_link(PieceCopy a,
                                                            const int32_t *__restrict__ pages,
                                                            const int64_t *__restrict__ slot_idx,
                                                            InlineIdx inl) {
-  piece_copy<DIR, INLINE, VEC>(a, pages, slot_idx, &inl);
+  piece_copy<DIR, INLINE, VEC, true>(a, pages, slot_idx, &inl);
 }
 template <int DIR, bool INLINE, int VEC>
 __global__ __launch_bounds__(kThreads) void copy_hbm(PieceCopy a, const int32_t *__restrict__ pages,
                                                      const int64_t *__restrict__ slot_idx,
                                                      InlineIdx inl) {
-  if (INLINE && a.part_shift > 0) return piece_parts<DIR, VEC>(a, inl.pages);
-  piece_copy<DIR, INLINE, VEC>(a, pages, slot_idx, &inl);
+  if constexpr (INLINE && VEC == 4) {
+    if (a.part_shift > 0) return piece_parts<DIR, VEC>(a, inl.pages);
+  }
+  piece_copy<DIR, INLINE, VEC, false>(a, pages, slot_idx, &inl);
 }
 // The HBM gather/scatter with the page ids of up to kArgPagesMax entries in
 // the kernel arguments (slot of entry i is i): the same loop reads them as
@@ -245,8 +254,10 @@ __global__ __launch_bounds__(kThreads) void copy_hbm(PieceCopy a, const int32_t 
 // the host would have to track.
 template <int DIR, int VEC>
 __global__ __launch_bounds__(kThreads) void copy_hbm_args(PieceCopy a, ArgPages ids) {
-  if (a.part_shift > 0) return piece_parts<DIR, VEC>(a, ids.pages);
-  piece_copy<DIR, false, VEC>(a, ids.pages, nullptr, nullptr);
+  if constexpr (VEC == 4) {
+    if (a.part_shift > 0) return piece_parts<DIR, VEC>(a, ids.pages);
+  }
+  piece_copy<DIR, false, VEC, false>(a, ids.pages, nullptr, nullptr);
 }
 
 // Consumer stand-in of the layered load: wave w of the grid folds the
@@ -373,10 +384,12 @@ hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const Arg
                              int dir, int route, int64_t workgroups, hipStream_t stream) {
   const int64_t units = a.n * a.layer_count;
   if (units <= 0) return hipSuccess;
-  // parts: 32-bit work items, page ids in the arguments
+  // parts: 32-bit work items, page ids in the arguments, pieces of a whole
+  // round of loads or more
   if (a.part_shift < 0 || a.part_shift > 30 ||
       (a.part_shift > 0 && ((units << a.part_shift) > INT32_MAX || a.part_vecs < 1 ||
-                            route != kRouteHbm || (inl == nullptr && ids == nullptr))))
+                            a.piece_bytes < 16 * 4 * kWave || route != kRouteHbm ||
+                            (inl == nullptr && ids == nullptr))))
     return hipErrorInvalidValue;
   if (a.num_xcd < 1 || a.num_xcd > 32 || a.xcd_mask == 0 ||
       (a.num_xcd < 32 && (a.xcd_mask >> a.num_xcd) != 0))

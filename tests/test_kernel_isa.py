@@ -108,6 +108,18 @@ def test_argument_blocks_fit_what_the_runtime_takes(assembly):
     assert all(v >= 8192 for v in args.values()), args
 
 
+def test_hbm_copies_spill_no_registers(assembly):
+    # not even scalar registers into lanes of a vector register: the copy
+    # loops of the HBM gather and scatter are short enough for that to show
+    text = assembly["ea_copy_kernels.hip"]
+    spills = {m.group(1): (int(m.group(2)), int(m.group(3))) for m in re.finditer(
+        r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.sgpr_spill_count:\s+(\d+)\n(?:.*\n)*?"
+        r"\s+\.vgpr_spill_count:\s+(\d+)", text)}
+    hbm = {n: v for n, v in spills.items() if "copy_hbm" in n}
+    assert len(hbm) == 18, sorted(hbm)
+    assert not any(any(v) for v in hbm.values()), hbm
+
+
 # ---------------------------------------------------------------- DPP hazards
 # A DPP instruction needs every VGPR it reads to have been written by a
 # VALU instruction at least two wait states earlier, and an EXEC write at
