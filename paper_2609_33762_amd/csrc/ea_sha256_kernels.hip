@@ -765,6 +765,12 @@ __global__ __launch_bounds__(kPpThreads) void sha256_chain_pair_split(
 // key of a launch has the same number of blocks, so the rows stay in step.
 // Rows past the last key rerun row 0's tokens and store nothing.
 //
+// The schedule waves run at raised priority: from three workgroups on a
+// compute unit one shares its SIMD with a rounds wave, which leaves hardly an
+// issue slot free and waits for a schedule wave in the end.  3,090 to 4,096
+// keys of 1,024 tokens take 155 us a call without it, with it 111; up to two
+// workgroups per unit nothing changes (2,040 keys 110 and 109).
+//
 // LDS in 32-bit words: two halves of kMsHalf words, row r's K_t + W_t at
 // 64 r of each, then the 64 ones the a-lanes read as their K + W.
 constexpr int kMsHalf = 64 * kSpRows;
@@ -801,6 +807,7 @@ __global__ __launch_bounds__(128) void sha256_midstates_split(
   ok = ok || row == 0;
   const int32_t blocks = block_tokens / 16;
   if (wave == 1) {
+    __builtin_amdgcn_s_setprio(3);
     // lane j of row r: word j of the row's current block, W_16+j, W_32+j and
     // W_48+j in turn; the next block's token read one block ahead
     lds[kMsOnes + lane] = 1u;

@@ -243,3 +243,15 @@ def test_two_lane_chain_waves_share_one_start_and_one_barrier_count(assembly):
             elif op not in ("s_waitcnt", "s_nop"):
                 run = 0
         assert best >= 13, (name, best)
+
+
+def test_schedule_waves_that_share_simds_run_at_raised_priority(assembly):
+    # forms that put several workgroups on a compute unit: a rounds wave would
+    # keep its SIMD from the schedule wave that others wait for
+    bodies, _, _ = kernels(assembly["ea_sha256_kernels.hip"])
+    shared = {n: b for n, b in bodies.items()
+              if "sha256_midstates_split" in n or "sha256_chain_pair_split" in n}
+    assert len(shared) == 4, sorted(shared)
+    for name, body in shared.items():
+        prio = [rest.strip() for op, rest, _ in _instructions(body) if op == "s_setprio"]
+        assert prio == ["3"], (name, prio)
