@@ -540,6 +540,16 @@ ea::PieceCopy base_copy(const ea_cache *c, int64_t slot_bytes, int32_t chunk) {
   return a;
 }
 
+// Layered loads of at least this many layers read their indices from device
+// memory: each layer's kernel would wait for them over the link before its
+// first piece, and the copy ahead of the first layer costs 3-5 us.  48 layers
+// of 4 KiB pieces, us a layer without and with it: 40 pages 10.9 / 9.7, 128
+// 18.4 / 16.7, 4,096 302.0 / 300.4; whole calls of 200 pages of 4 KiB pieces
+// with 24 / 8 / 4 / 2 layers 643 / 223 / 111 / 59 and 572 / 201 / 106 / 59 us,
+// 33 pages 268 / 98 / 52 / 30 and 246 / 95 / 53 / 33, 1,500 pages of 1 KiB
+// 1,157 / 399 / 202 / 106 and 1,152 / 398 / 206 / 116.
+constexpr int32_t kTwinLayers = 8;
+
 // Launch a piece copy for n (slot, page) entries, one per page (slots null:
 // entry i goes to slot i / a.chunk): small batches carry their indices in
 // the kernel arguments, and so do the page ids of HBM copies of up to
@@ -815,7 +825,7 @@ int ea_tier_create_chunked(const ea_cache *shape, int32_t chunk_pages, int64_t c
     const int nx = t->num_xcd;
     t->xcd_store = xcd_mask_from_env("EA_XCD_STORE", nx >= 4 ? 0x5u : 0x1u, nx);
     t->xcd_load = xcd_mask_from_env("EA_XCD_LOAD", nx >= 4 ? 0xAu : (nx > 1 ? 0x2u : 0x1u), nx);
-    t->res[EA_DIR_LOAD].ring.keep_twins();  // for layered loads
+    if (t->num_layers >= kTwinLayers) t->res[EA_DIR_LOAD].ring.keep_twins();
     t->grid_gather = grid_hbm(ea::kToSlots);
     t->grid_scatter = grid_hbm(ea::kToPages);
     // a layered load is one short kernel per layer: 16 workgroups hide the
@@ -1158,11 +1168,9 @@ int ea_load_blocks_layered(ea_tier *t, ea_cache *c, const int64_t *host_slots,
       }
       pin = &inl;
     } else {
-      // Read by every layer's kernel, each of which would wait for them over
-      // the link before its first piece.  48 layers of 4 KiB pieces, us a
-      // layer: 40 pages 10.9 -> 9.7, 128 18.4 -> 16.7, 4,096 302.0 -> 300.4.
       EA_TRY(ring.upload(each.data(), dst_pages, m, &a.slot_idx, &a.pages, &region));
-      EA_TRY(ring.to_device(region, m, &a.slot_idx, &a.pages, copy_stream));
+      if (c->d.num_layers >= kTwinLayers)
+        EA_TRY(ring.to_device(region, m, &a.slot_idx, &a.pages, copy_stream));
     }
     if (t->d_busy != nullptr) {
       a.link_flag = t->d_busy;
