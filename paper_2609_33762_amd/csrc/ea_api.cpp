@@ -534,6 +534,7 @@ ea::PieceCopy base_copy(const ea_cache *c, int64_t slot_bytes, int32_t chunk) {
   a.num_layers = c->d.num_layers;
   a.layer_begin = 0;
   a.layer_count = c->d.num_layers;
+  a.scale_layers = 1;
   a.num_xcd = c->num_xcd;
   a.xcd_mask = all_xcds(c->num_xcd);
   a.hw_xcd = c->hw_xcd;
@@ -550,6 +551,19 @@ ea::PieceCopy base_copy(const ea_cache *c, int64_t slot_bytes, int32_t chunk) {
 // 1,157 / 399 / 202 / 106 and 1,152 / 398 / 206 / 116.
 constexpr int32_t kTwinLayers = 8;
 
+// Layers whose scale words one unit moves (PieceCopy::scale_layers) in a copy
+// of all layers.  Reads of the slots gain by eight at a time, layered loads
+// most (4,096 pages of 4 KiB pieces 310.6 us a layer -> 302.1, of 16 KiB
+// 1,184.8 -> 1,175.9; 400 pages of 48 layers in 4 KiB pieces loaded at once
+// 1,454 -> 1,435).  Stores over the host link gain with pieces of up to 2 KiB
+// (400 pages of 48 x 1 KiB 685 -> 640 us, of 2 KiB 797 -> 750) and lose above,
+// where the 64-byte write comes in between long runs of the pieces' own (of 3
+// KiB 1,098 -> 1,136, of 8 KiB 2,855 -> 2,912, of 16 KiB 5,649 -> 5,773).
+int32_t scale_group(int64_t chunk, int64_t piece, int dir, int route) {
+  if (chunk != 1) return 1;
+  return dir == ea::kToSlots && route == ea::kRouteHostLink && piece > 2048 ? 1 : 8;
+}
+
 // Launch a piece copy for n (slot, page) entries, one per page (slots null:
 // entry i goes to slot i / a.chunk): small batches carry their indices in
 // the kernel arguments, and so do the page ids of HBM copies of up to
@@ -559,6 +573,7 @@ int launch_entries(ea::PieceCopy a, IndexRing &ring, const int64_t *slots,
                    const int32_t *pages, int64_t n, int dir, int route, int64_t grid,
                    hipStream_t s) {
   a.n = n;
+  a.scale_layers = scale_group(a.chunk, a.piece_bytes, dir, route);
   if (route == ea::kRouteHbm) {
     // page ids in the arguments and units in entry order: parts may be used
     const bool parts = !slots && !a.layer_major &&
@@ -1157,6 +1172,7 @@ int ea_load_blocks_layered(ea_tier *t, ea_cache *c, const int64_t *host_slots,
     a.xcd_mask = t->xcd_load;
     a.n = m;
     a.layer_count = 1;
+    a.scale_layers = scale_group(t->chunk, t->piece, ea::kToPages, ea::kRouteHostLink);
     ea::InlineIdx inl;
     const ea::InlineIdx *pin = nullptr;
     IndexRing &ring = t->res[EA_DIR_LOAD].ring;

@@ -69,20 +69,18 @@ __device__ __forceinline__ void copy_unit(const PieceCopy &a, int64_t l, int64_t
   // The scale words are read before the piece, so that their round trip
   // (over the host link for a load) overlaps the piece's instead of following
   // it.  With one page per slot the words of a page's layers are neighbours
-  // in the slot, so every eighth layer's unit takes eight of them along, one
-  // per lane: one 64-byte access of the host link instead of eight of 8 bytes.
-  // A layered load of 4,096 pages in 4 KiB pieces: 310.6 -> 302.1 us a layer
-  // (54.1 -> 55.7 GB/s), in 16 KiB pieces 1,184.8 -> 1,175.9.
+  // in the slot, and with a.scale_layers = 8 every eighth layer's unit takes
+  // eight of them along, one per lane: one 64-byte access of the slots instead
+  // of eight of 8 bytes.
+  const bool scales = a.scales != nullptr && v0 == 0;
   uint64_t *cs = nullptr, *ss = nullptr;
   uint64_t scale = 0;
-  const bool grouped = a.chunk == 1;
-  const bool scaled = a.scales != nullptr && v0 == 0 &&
-                      (grouped ? (l & 7) == 0 && lane < 8 && l + lane < a.num_layers : lane == 0);
-  if (scaled) {
-    const int64_t ls = grouped ? l + lane : l;
-    cs = reinterpret_cast<uint64_t *>(a.scales + (ls * a.num_pages + page) * 8);
-    ss = reinterpret_cast<uint64_t *>(slot_base + a.payload_bytes + (ls * a.chunk + c) * 8);
-    scale = DIR == kToSlots ? *cs : *ss;
+  int words = 0;  // the same in every lane
+  if (scales) {
+    cs = reinterpret_cast<uint64_t *>(a.scales + (l * a.num_pages + page) * 8);
+    ss = reinterpret_cast<uint64_t *>(slot_base + a.payload_bytes + at * 8);
+    if (((int)l & (a.scale_layers - 1)) == 0) words = min(a.scale_layers, a.num_layers - (int)l);
+    if (lane < words) scale = DIR == kToSlots ? cs[lane * a.num_pages] : ss[lane];
   }
   for (int64_t base = v0; base < nvec; base += (int64_t)kWave * VEC) {
     u32x4 r[VEC];
@@ -97,10 +95,8 @@ __device__ __forceinline__ void copy_unit(const PieceCopy &a, int64_t l, int64_t
       if (v < nvec) store_nt(dst + v, r[k]);
     }
   }
-  if (scaled) {
-    if (DIR == kToSlots) *ss = scale; else *cs = scale;
-  }
-  if (a.scales != nullptr && v0 == 0) {
+  if (scales) {
+    if (lane < words) *(DIR == kToSlots ? ss + lane : cs + lane * a.num_pages) = scale;
     if (DIR == kToSlots && at == 0) {  // once per slot
       const int64_t pad_begin = a.payload_bytes + 8 * (int64_t)a.num_layers * a.chunk;
       const int64_t pad_words = (a.slot_bytes - pad_begin) >> 3;
@@ -384,6 +380,8 @@ hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const Arg
                              int dir, int route, int64_t workgroups, hipStream_t stream) {
   const int64_t units = a.n * a.layer_count;
   if (units <= 0) return hipSuccess;
+  // scale words of one layer, or of eight where they are neighbours
+  if (a.scale_layers != 1 && (a.scale_layers != 8 || a.chunk != 1)) return hipErrorInvalidValue;
   // parts: 32-bit work items, page ids in the arguments, pieces of a whole
   // round of loads or more
   if (a.part_shift < 0 || a.part_shift > 30 ||

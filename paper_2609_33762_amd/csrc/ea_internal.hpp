@@ -39,6 +39,11 @@ struct PieceCopy {
   int32_t chunk;             // C >= 1
   int32_t layer_begin;
   int32_t layer_count;
+  // 1: every unit moves its own scale word.  8 (one page per slot only): the
+  // units of layers 0, 8, .. move the words of eight layers each, also those
+  // outside [layer_begin, layer_begin + layer_count), and the others none, so
+  // the launches of one copy must cover all layers, in order on one stream.
+  int32_t scale_layers;
   int32_t identity_slots;    // slot of entry i is i / C (staging buffers)
   int32_t layer_major;       // units ordered layer by layer, else entry by entry
   // HBM copies with identity slots whose units are too few to fill the chip:

@@ -1,5 +1,5 @@
-// The host side of a layered load (ea_load_blocks_layered) on a stand-in for
-// the HIP runtime, meant to be built with AddressSanitizer and
+// The host side of loads, layered loads and stores on a stand-in for the HIP
+// runtime, meant to be built with AddressSanitizer and
 // UndefinedBehaviorSanitizer.
 //
 // Test infrastructure only: it links the product's ea_api.cpp and
@@ -10,7 +10,9 @@
 // without device memory for their index arrays, must leave no error behind
 // for the caller's next runtime call, and must allocate nothing once a plain
 // load of as many pages has run.  Caches of few layers, whose calls the copy to
-// device memory would only make longer, must make none.
+// device memory would only make longer, must make none.  Scale words must
+// arrive whether units move their own or groups of eight, which is chosen by
+// direction and piece size.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -32,6 +34,7 @@ int64_t g_allocations = 0;
 hipError_t g_last = hipSuccess;
 std::map<const uint8_t *, size_t> g_device;  // live device allocations and their sizes
 int64_t g_from_device = 0;  // copies whose index arrays lie in device memory
+int32_t g_scale_layers = 0;  // of the last copy
 
 hipError_t done(hipError_t e) {
   if (e != hipSuccess) g_last = e;
@@ -104,17 +107,26 @@ hipError_t launch_layer_checksum(const uint8_t *, const uint8_t *, int64_t, int6
                                  const int32_t *, int32_t, uint64_t *, hipStream_t) {
   return hipSuccess;
 }
-// One page per slot, no scales: the pieces of layers [begin, begin + count).
+// The pieces and scale words of layers [begin, begin + count), as the kernel
+// takes them: entry i is page i % C of its slot.
 hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const ArgPages *, int dir,
                              int, int64_t, hipStream_t) {
   if (inl == nullptr && in_device(a.pages) && in_device(a.slot_idx)) ++g_from_device;
+  g_scale_layers = a.scale_layers;
+  const auto move = [dir](uint8_t *cache, uint8_t *slot, int64_t n) {
+    std::memcpy(dir == kToSlots ? slot : cache, dir == kToSlots ? cache : slot, (size_t)n);
+  };
   for (int64_t i = 0; i < a.n; ++i) {
     const int64_t page = inl ? inl->pages[i] : a.pages[i];
-    const int64_t slot = inl ? inl->slots[i] : a.slot_idx[i];
+    uint8_t *slot = a.slots + (inl ? inl->slots[i] : a.slot_idx[i]) * a.slot_bytes;
     for (int64_t l = a.layer_begin; l < a.layer_begin + a.layer_count; ++l) {
-      uint8_t *c = a.cache + (l * a.num_pages + page) * a.piece_bytes;
-      uint8_t *s = a.slots + slot * a.slot_bytes + l * a.piece_bytes;
-      std::memcpy(dir == kToSlots ? s : c, dir == kToSlots ? c : s, (size_t)a.piece_bytes);
+      const int64_t at = l * a.chunk + i % a.chunk;
+      move(a.cache + (l * a.num_pages + page) * a.piece_bytes, slot + at * a.piece_bytes,
+           a.piece_bytes);
+      if (a.scales == nullptr || l % a.scale_layers != 0) continue;
+      for (int64_t k = 0; k < a.scale_layers && l + k < a.num_layers; ++k)
+        move(a.scales + ((l + k) * a.num_pages + page) * 8,
+             slot + a.payload_bytes + (at + k * a.chunk) * 8, 8);
     }
   }
   return hipSuccess;
@@ -190,6 +202,60 @@ struct Rig {
   }
 };
 
+// Pages and scale words through store, load and layered load, and the group
+// of layers whose words move together each way.
+void scale_words(int32_t layers, int32_t head_dim, int32_t chunk, int32_t n, int32_t group_out,
+                 int32_t group_in) {
+  const int64_t piece = 32 * (int64_t)head_dim, pages = 3 * n * chunk;
+  std::vector<uint8_t> kv((size_t)(layers * pages * piece)), sc((size_t)(layers * pages * 8));
+  std::mt19937 r((unsigned)(layers * 131 + head_dim + chunk));
+  for (auto &b : kv) b = (uint8_t)r();
+  for (auto &b : sc) b = (uint8_t)r();
+  ea_cache_desc d{};
+  d.base = kv.data();
+  d.scale_base = sc.data();
+  d.num_pages = (int32_t)pages;
+  d.num_layers = layers;
+  d.page_tokens = 16;
+  d.num_kv_heads = 1;
+  d.head_dim = head_dim;
+  d.elem_bytes = 1;
+  ea_cache *cache = nullptr;
+  ea_tier *tier = nullptr;
+  if (ea_cache_create(&d, &cache) != EA_OK) fail("cache", n);
+  const int64_t slot = layers * chunk * piece + (layers * chunk * 8 + 255) / 256 * 256;
+  if (ea_tier_create_chunked(cache, chunk, n * slot, -1, &tier) != EA_OK) fail("tier", n);
+  std::vector<hipEvent_t> events((size_t)layers);
+  for (auto &e : events) (void)hipEventCreate(&e);
+  std::vector<int64_t> slots((size_t)n);
+  std::vector<int32_t> ids((size_t)pages);
+  std::iota(slots.begin(), slots.end(), 0);
+  std::iota(ids.begin(), ids.end(), 0);
+  std::shuffle(slots.begin(), slots.end(), r);
+  std::shuffle(ids.begin(), ids.end(), r);
+  const int32_t m = n * chunk;
+  std::vector<uint8_t> want = kv, want_sc = sc;
+  for (int32_t i = 0; i < 2 * m; ++i)
+    for (int64_t l = 0; l < layers; ++l) {
+      const int64_t from = l * pages + ids[i % m], to = l * pages + ids[m + i];
+      std::memcpy(&want[to * piece], &kv[from * piece], (size_t)piece);
+      std::memcpy(&want_sc[to * 8], &sc[from * 8], 8);
+    }
+  if (ea_store_blocks(cache, tier, ids.data(), slots.data(), nullptr, n, nullptr) != EA_OK)
+    fail("store", n);
+  if (g_scale_layers != group_out) fail("group of the store", head_dim);
+  if (ea_load_blocks(tier, cache, slots.data(), ids.data() + m, n, nullptr) != EA_OK)
+    fail("load", n);
+  if (g_scale_layers != group_in) fail("group of the load", head_dim);
+  if (ea_load_blocks_layered(tier, cache, slots.data(), ids.data() + 2 * m, n, nullptr,
+                             events.data(), layers) != EA_OK)
+    fail("layered load", n);
+  if (g_scale_layers != group_in) fail("group of the layered load", head_dim);
+  if (kv != want || sc != want_sc) fail("pages or scales differ", n);
+  for (auto &e : events) (void)hipEventDestroy(e);
+  if (ea_tier_destroy(tier) != EA_OK || ea_cache_destroy(cache) != EA_OK) fail("destroy", n);
+}
+
 }  // namespace
 
 int main() {
@@ -224,6 +290,14 @@ int main() {
     if (g_allocations != allocations) fail("allocated again", 40);
     if (g_from_device != before + (layers >= 8 ? 3 * layers : 0)) fail("indices copied", layers);
   }
+  // pieces of 2,048 bytes and the next larger ones; layers around the groups'
+  // ends; one page per slot, and chunks, whose words are not neighbours
+  for (int32_t layers : {1, 7, 8, 9, 17})
+    for (int32_t n : {3, 40}) {
+      scale_words(layers, 64, 1, n, 8, 8);
+      scale_words(layers, 65, 1, n, 1, 8);
+      scale_words(layers, 2, 16, n, 1, 1);
+    }
   if (!g_device.empty()) fail("device memory left", 0);
   std::puts("ok");
   return 0;

@@ -14,9 +14,10 @@ for full blocks; store then load reproduces pages and scales).  Planted
 mistakes in a scratch copy of the tier (trimming one clock unit too much, a
 hit not promoted) are caught by these seeds.
 
-tests/sanitize/layered_indices.cpp runs the host side of the layered load on
-a stand-in for the HIP runtime whose device memory can run out: the call then
-works as it does with it.
+tests/sanitize/transfers_host.cpp runs the host side of stores, loads and
+layered loads on a stand-in for the HIP runtime whose device memory can run
+out: layered loads then work as they do with it, and scale words move in the
+groups chosen for each direction and size.
 """
 import os
 import shutil
@@ -73,16 +74,16 @@ def test_long_stream_with_bounded_history_under_sanitizers(fuzz_binary):
     run(fuzz_binary, 99, 80_000)
 
 
-def test_layered_load_with_and_without_device_memory_for_its_indices(tmp_path):
+def test_transfers_on_a_stand_in_runtime(tmp_path):
     if not shutil.which("g++"):
         pytest.skip("g++ not available")
     if not os.path.exists(os.path.join(HIP_INCLUDE, "hip", "hip_runtime_api.h")):
         pytest.skip("HIP headers not available")
-    exe = str(tmp_path / "layered_indices")
+    exe = str(tmp_path / "transfers_host")
     subprocess.run(["g++", "-std=c++17"] + FLAGS +
                    ["-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
                     "-I", HIP_INCLUDE, "-I", CSRC,
-                    os.path.join(ROOT, "tests", "sanitize", "layered_indices.cpp"),
+                    os.path.join(ROOT, "tests", "sanitize", "transfers_host.cpp"),
                     os.path.join(CSRC, "ea_api.cpp"), os.path.join(CSRC, "ea_tier_meta.cpp"),
                     "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
