@@ -113,7 +113,7 @@ def test_device_calls_back_to_back():
 def test_every_chain_form(form, monkeypatch):
     # the chained compression runs two lanes per sequence, one lane per
     # sequence (large batches), a workgroup of two waves per four sequences
-    # (up to eight sequences per compute unit), or, for the largest batches, one lane
+    # (up to four sequences per compute unit), or, for the largest batches, one lane
     # per sequence for token blocks and chain alike (fused); each form forced
     # on ragged chains, parents, chunk-sized blocks, a long chain and the
     # extreme token values
@@ -183,9 +183,9 @@ def test_two_lane_pairs_of_unequal_length(first, second, wide, monkeypatch):
 
 
 def test_batch_past_the_one_lane_threshold():
-    # more sequences than two-lane waves fit one per SIMD (32 per SIMD):
-    # the library picks the one-lane chain by itself; ragged lengths, parents;
-    # past 256 sequences per compute unit it picks the fused form
+    # past 128 sequences per compute unit (two workgroups of the two-lane form
+    # on each) the library picks the one-lane chain by itself; ragged lengths,
+    # parents; from 256 sequences per compute unit it picks the fused form
     r = W.rng(95)
     check(list(r.integers(0, 160, size=40000)), 16, parents=True, seed=95)
     check([64] * 40000, 16, seed=96)
@@ -213,7 +213,7 @@ def test_64_bit_offsets(form, monkeypatch):
 
 
 def test_few_long_chains_take_the_split_form():
-    # up to eight sequences per compute unit the library picks the two-wave
+    # up to four sequences per compute unit the library picks the two-wave
     # form by itself: ragged long chains with parents, a chain of one key,
     # empty sequences
     r = W.rng(101)
@@ -236,15 +236,18 @@ def test_split_rows_of_unequal_length(lengths, monkeypatch):
     check(lengths, 16, seed=130 + len(lengths))
 
 
+@pytest.mark.parametrize("per_cu", [4, 128])
 @pytest.mark.parametrize("extra", [0, 1])
-def test_split_form_threshold(extra):
-    # eight sequences per compute unit (the last batch of the two-wave form)
-    # and one more (the first of the two-lane form), ragged chains of up to
-    # 40 keys with parents
+def test_chain_form_thresholds(per_cu, extra):
+    # four sequences per compute unit (the last batch of the two-wave form,
+    # then the first of the two-lane form) and 128 (the last batch of the
+    # two-lane form, its workgroups full, then the first of the one-lane
+    # form): ragged chains with parents
     torch = need_gpu()
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    r = W.rng(102 + extra)
-    lengths = [int(x) for x in r.integers(0, 640, size=8 * cus + extra)]
+    r = W.rng(102 + per_cu + extra)
+    lengths = [int(x) for x in r.integers(0, 640 if per_cu == 4 else 160,
+                                          size=per_cu * cus + extra)]
     check(lengths, 16, parents=True, seed=102 + extra)
 
 
