@@ -46,11 +46,17 @@ __device__ __forceinline__ void store_nt(u32x4 *p, u32x4 v) { __builtin_nontempo
 // Unit u is (entry i, layer l): entry-major (u = i * layer_count + l - b,
 // a page's layers one after the other) or, with a.layer_major, layer-major
 // (u = (l - b) * n + i, every entry of one layer first); b = layer_begin.
+// Copies over the host link (LINK) are always entry-major: without the other
+// order's 64-bit divisions their kernels are a third shorter, which counts
+// where a wave has few units (a layer of 32 pieces of 16 KiB 16.97 us -> 16.75,
+// 25,344 pieces of 1 KiB stored 772 us -> 755).
+template <bool LINK>
 __device__ __forceinline__ int64_t unit_entry(const PieceCopy &a, int64_t u) {
-  return a.layer_major ? u % a.n : u / a.layer_count;
+  return !LINK && a.layer_major ? u % a.n : u / a.layer_count;
 }
+template <bool LINK>
 __device__ __forceinline__ int64_t unit_layer(const PieceCopy &a, int64_t u, int64_t i) {
-  return a.layer_begin + (a.layer_major ? u / a.n : u - i * a.layer_count);
+  return a.layer_begin + (!LINK && a.layer_major ? u / a.n : u - i * a.layer_count);
 }
 
 // Copy the piece of layer l of entry i, whose page and slot the caller has
@@ -155,9 +161,9 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
   if constexpr (INLINE) {
     // indices from the kernel arguments (scalar loads, u is wave-uniform)
     for (int64_t u = first; u < units; u += waves) {
-      const int64_t i = unit_entry(a, u);
+      const int64_t i = unit_entry<LINK>(a, u);
       const uint32_t busy = LINK ? link_busy(a) : 0;
-      copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, inl->pages[i], inl->slots[i], lane,
+      copy_unit<DIR, INLINE, VEC>(a, unit_layer<LINK>(a, u, i), i, inl->pages[i], inl->slots[i], lane,
                                   0, a.piece_bytes >> 4);
       if (LINK) yield_link(a, busy, debt);
     }
@@ -174,19 +180,19 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
       int32_t vpage = 0;
       int64_t vslot = 0;
       if (ul < units) {
-        const int64_t il = unit_entry(a, ul);
+        const int64_t il = unit_entry<LINK>(a, ul);
         vpage = pages[il];
         vslot = a.identity_slots ? (int64_t)((uint32_t)il / (uint32_t)a.chunk) : slot_idx[il];
       }
       for (int k = 0; k < kWave; ++k) {
         const int64_t u = u0 + (int64_t)k * waves;
         if (u >= units) break;
-        const int64_t i = unit_entry(a, u);
+        const int64_t i = unit_entry<LINK>(a, u);
         const int64_t page = __builtin_amdgcn_readlane(vpage, k);
         const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)vslot, k);
         const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)vslot >> 32), k);
         const uint32_t busy = LINK ? link_busy(a) : 0;
-        copy_unit<DIR, INLINE, VEC>(a, unit_layer(a, u, i), i, page,
+        copy_unit<DIR, INLINE, VEC>(a, unit_layer<LINK>(a, u, i), i, page,
                                     (int64_t)(((uint64_t)hi << 32) | lo), lane, 0,
                                     a.piece_bytes >> 4);
         if (LINK) yield_link(a, busy, debt);
@@ -394,6 +400,7 @@ hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const Arg
     return hipErrorInvalidValue;
   // entry indices and chunk positions are computed in 32 bits
   if (a.chunk < 1 || a.n > INT32_MAX) return hipErrorInvalidValue;
+  if (a.layer_major && route != kRouteHbm) return hipErrorInvalidValue;
   // page ids in the arguments: HBM route, identity slots, all ids there
   if (ids != nullptr && (inl != nullptr || route != kRouteHbm || !a.identity_slots ||
                          a.n > kArgPagesMax))

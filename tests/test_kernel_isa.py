@@ -120,6 +120,19 @@ def test_hbm_copies_spill_no_registers(assembly):
     assert not any(any(v) for v in hbm.values()), hbm
 
 
+def test_host_link_copies_hold_one_unit_order(assembly):
+    # the layer-by-layer order and its 64-bit divisions belong to the HBM
+    # copies alone: the host-link kernels, which also hold the link's
+    # priority, stay shorter than their HBM twins
+    bodies, _, _ = kernels(assembly["ea_copy_kernels.hip"])
+    length = {n: len(_instructions(b)) for n, b in bodies.items()}
+    link = {n: v for n, v in length.items() if "copy_host_link" in n}
+    assert len(link) == 12, sorted(link)
+    for n, v in link.items():
+        twin = n.replace("14copy_host_link", "8copy_hbm")
+        assert v < length[twin], (n, v, length[twin])
+
+
 # ---------------------------------------------------------------- DPP hazards
 # A DPP instruction needs every VGPR it reads to have been written by a
 # VALU instruction at least two wait states earlier, and an EXEC write at
