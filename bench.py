@@ -1707,13 +1707,11 @@ def run_tp8_shard(args):
                  {"tp8_shard": out, "beta_bytes_per_token": beta})
 
 
-# Lane-instructions per key with 16-token blocks in one-lane form, counted
-# in the library's gfx950 assembly (loop bodies): 1,410 for the token block
-# (sha256_midstates) and 1,378 for the chained compression
-# (sha256_chain_lane).  This is the work of a key; the two-lane chain form
-# issues 2 x 1,162 lane-instructions for the same compression, and that
-# surplus counts as overhead, not as work.
-HASH_INSTR_PER_KEY = 1410 + 1378
+# VALU instructions per key with 16-token blocks of the kernel the roofline is
+# taken on, counted in the library's gfx950 assembly (the key loop of
+# sha256_fused_scan for one-block keys: token block, chained compression, key
+# store).
+HASH_INSTR_PER_KEY = 2739
 # Integer VALU peak of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (a
 # wave64 instruction occupies a SIMD for 4 cycles; the 157.3 TFLOP/s fp32
 # figure counts packed two-wide FMAs, which integer ops do not have).
@@ -1724,12 +1722,12 @@ def run_hash(args):
     """Chained keys (16-token blocks) on the device, tokens already in HBM:
     the turn's 56k-token prompt (one 3,500-key chain, and in 1,024-token
     chunks: 54 keys of 64 token blocks each), one 64k-token sequence, 64
-    such sequences (these three in the two-wave form, one workgroup per
-    sequence), 16,384 sequences of 1,024 tokens (the two-lane chain kernel
-    then has 512 waves for the 1,024 SIMDs) and 65,536 of 256 tokens (more
-    than 32 sequences per SIMD, so the chain runs one lane per sequence:
-    1,024 waves); every run checked against the host entry point's keys.
-    The roofline is taken on the last."""
+    such sequences (these three in the two-wave form, four sequences per
+    workgroup), 16,384 sequences of 1,024 tokens (the two-lane form, one
+    workgroup of four waves per compute unit) and 65,536 of 256 tokens (256
+    sequences per compute unit, so token blocks and chain run fused, one lane
+    per sequence: 1,024 waves); every run checked against the host entry
+    point's keys.  The roofline is taken on the last."""
     import torch
     torch.cuda.set_device(0)
     out = {}

@@ -123,8 +123,14 @@ int64_t grid_hbm(int dir) {
 //    loads) on 1,024 workgroups.  8 pages of 32 x 64 KiB 19.8 / 21.1 -> 8.2 /
 //    8.3 (then bound by the host's calls); 48 of them (101 MB) 40.8 / 48.6 ->
 //    36.3 / 40.3; 48 pages of 48 x 32 KiB (75 MB) 33.7 / 37.0 -> 28.0 / 30.6;
-//    200 of 48 x 8 KiB (79 MB) 29.9 / 37.2 -> 29.5 / 31.9.  At 157 MB the
-//    gather of 8 KiB pieces loses (56.6 -> 58.0).
+//    105 MiB of 32 layers in 8 KiB pieces 41.8 / 48.7 -> 41.7 / 45.4.  At 157
+//    MB the gather of 8 KiB pieces loses (56.6 -> 58.0).  Pieces of 4 KiB or
+//    less stay whole and gain by the grid alone, the scatter most: 48 MiB in 1
+//    / 2 / 4 KiB pieces 33.0 / 51.3, 22.6 / 34.2, 20.7 / 24.9 -> 23.9 / 24.3,
+//    20.9 / 22.8, 20.6 / 22.4; 4 MiB within 0.3 us.  The staged plan's halves
+//    take the same shapes beside the copy engine: stores / loads of one 2 MiB
+//    page 73 / 309 -> 64 / 298 us, of eight 339 / 364 -> 327 / 351, of 48 MiB
+//    and more the same.
 //  - Pieces of 64 KiB and more: parts of 16 KiB on 512 workgroups at any size
 //    (1,500 pages of 32 x 64 KiB 1,100 / 1,161 -> 1,014 / 1,037); cutting
 //    32 KiB or 40 KiB pieces of large copies loses 2-7%.
@@ -132,7 +138,8 @@ int64_t grid_hbm(int dir) {
 //    two workgroups per CU, the scatter (sequential reads, random writes) on
 //    one, since more random writes in flight lower its rate, except pieces of
 //    4 KiB or less, which leave too few bytes in flight (2,048 pages of 48 x
-//    4 KiB: 180 us on 256 workgroups, 157 on 512).
+//    4 KiB: 180 us on 256 workgroups, 157 on 512; 1,706 of 32 x 3 KiB 113 and
+//    71).
 struct HbmShape {
   int64_t grid;
   int64_t part_bytes;  // 0: whole pieces

@@ -163,8 +163,8 @@ __device__ __forceinline__ void piece_copy(const PieceCopy &a, const int32_t *__
     for (int64_t u = first; u < units; u += waves) {
       const int64_t i = unit_entry<LINK>(a, u);
       const uint32_t busy = LINK ? link_busy(a) : 0;
-      copy_unit<DIR, INLINE, VEC>(a, unit_layer<LINK>(a, u, i), i, inl->pages[i], inl->slots[i], lane,
-                                  0, a.piece_bytes >> 4);
+      copy_unit<DIR, INLINE, VEC>(a, unit_layer<LINK>(a, u, i), i, inl->pages[i], inl->slots[i],
+                                  lane, 0, a.piece_bytes >> 4);
       if (LINK) yield_link(a, busy, debt);
     }
   } else {

@@ -46,9 +46,10 @@ struct PieceCopy {
   int32_t scale_layers;
   int32_t identity_slots;    // slot of entry i is i / C (staging buffers)
   int32_t layer_major;       // units ordered layer by layer, else entry by entry
-  // HBM copies with identity slots whose units are too few to fill the chip:
-  // each unit is cut into 1 << part_shift parts of part_vecs 16-byte vectors
-  // (the last ones shorter or empty).  0: whole units.
+  // HBM copies with identity slots whose units are too few to fill the chip,
+  // or whose pieces are of 64 KiB and more: each unit is cut into
+  // 1 << part_shift parts of part_vecs 16-byte vectors (the last ones shorter
+  // or empty).  0: whole units.
   int32_t part_shift;
   int32_t part_vecs;
   // Loads first on the host link.  link_flag is the tier's count of load
@@ -119,8 +120,6 @@ hipError_t probe_xcd_round_robin(int num_xcd, bool *ok);
 hipError_t launch_piece_copy(const PieceCopy &a, const InlineIdx *inl, const ArgPages *ids,
                              int dir, int route, int64_t workgroups, hipStream_t stream);
 
-// Add delta to a tier's load counter on `stream` (a one-lane kernel).
-
 // XOR checksum of one layer's piece of each of n pages (device page ids).
 hipError_t launch_layer_checksum(const uint8_t *cache, const uint8_t *scales, int64_t num_pages,
                                  int64_t piece_bytes, int32_t layer, const int32_t *pages,
@@ -149,13 +148,14 @@ hipError_t launch_sha256_fused(const int32_t *d_tokens, const void *d_key_offset
                                int32_t block_tokens, const uint8_t *d_parents, uint8_t *d_keys,
                                hipStream_t stream);
 
-// Key offsets from device sequence offsets d_seq_offsets [n_seqs+1], in two
-// kernels: d_key_offsets_out [n_seqs+1] (int64) and the hash kernels'
-// copies d_koff [n_seqs+1], d_toff [n_seqs] (int32 unless wide).  On
-// invalid offsets, or more than keys_cap keys, d_key_offsets_out[0] = -1
-// and d_koff is all zero (the hash kernels then write nothing).  d_state:
-// hash_scan_state_bytes(n_seqs) bytes of device memory whose first 8 bytes
-// are zero before the call (the kernels leave them zero again).
+// Key offsets from device sequence offsets d_seq_offsets [n_seqs+1], in one
+// kernel up to 16,384 sequences and in two beyond: d_key_offsets_out
+// [n_seqs+1] (int64) and the hash kernels' copies d_koff [n_seqs+1], d_toff
+// [n_seqs] (int32 unless wide).  On invalid offsets, or more than keys_cap
+// keys, d_key_offsets_out[0] = -1 and d_koff is all zero (the hash kernels then
+// write nothing).  d_state: hash_scan_state_bytes(n_seqs) bytes of device
+// memory whose first 8 bytes are zero before the call; the two kernels leave
+// them zero again, the one does not use it.
 hipError_t launch_hash_key_offsets(const int64_t *d_seq_offsets, int32_t n_seqs,
                                    int64_t n_tokens, int32_t block_tokens, int64_t keys_cap,
                                    int64_t *d_key_offsets_out, bool wide, void *d_koff,

@@ -25,7 +25,7 @@
 // three-input XOR and Ch/Maj one v_bitop3_b32 (gfx950's three-input logic
 // op), sums v_add3_u32.  Splitting the working state over two sides and the
 // schedule onto another wave brings the instructions of a chained
-// compression that are in line to about 700 from 1,378 in one lane.  The
+// compression that are in line to about 700 from 1,359 in one lane.  The
 // split costs lane-instructions, so once its waves would stack up on the
 // SIMDs the one-lane form finishes first.
 #include <hip/hip_runtime.h>
@@ -217,8 +217,9 @@ __global__ __launch_bounds__(256) void sha256_midstates(
   out[1] = make_uint4(st[4], st[5], st[6], st[7]);
 }
 
-// One sequence per workgroup of two waves: wave 0 runs the rounds, wave 1
-// the message schedule, handed over through LDS.
+// The row form: a workgroup of two waves carries four sequences, one per row
+// of 16 lanes.  Wave 0 runs the rounds, wave 1 the message schedule, handed
+// over through LDS.
 //
 // Rounds wave.  Lanes 0..3 of every row of 16 hold the a-side (a, b, c, d)
 // of the working state, lanes 12..15 the e-side (e, f, g, h); lanes 4..11
@@ -574,7 +575,8 @@ __global__ __launch_bounds__(128) void sha256_chain_split(
 // raised priority: where two workgroups share a CU (above 64 chains per CU) a
 // schedule wave has half as much to issue as the other one's rounds wave on
 // its SIMD, which waits for it anyway (18,000 chains of 64 keys 221 us,
-// raised 199; 24,576 of 128 keys 467 and 423).
+// raised 199; 24,576 of 128 keys 467 and 423).  With the longer asm blocks and
+// the unconditional midstate fetch these three take 552, 185 and 384 us.
 //
 // The hand-over goes through two LDS buffers of four words (K + W) per
 // chain: part p = words 16 + 4p .. 19 + 4p is written to buffer p & 1 and
@@ -884,7 +886,11 @@ __global__ __launch_bounds__(256) void sha256_chain_lane(
     n0 = mh[2 * k0];
     n1 = mh[2 * k0 + 1];
   }
-  // first midstate taken before the loop, as in the two-lane form
+  // Take the first midstate before the loop.  Loads and stores complete in
+  // issue order as far as the wait counter is concerned, so a load still
+  // pending at the loop head would make every key wait for the previous key's
+  // store to be acknowledged; with none pending there, a key waits only for
+  // the fetch of its midstate, issued a whole compression earlier.
   asm volatile("" ::"v"(n0.x), "v"(n0.y), "v"(n0.z), "v"(n0.w), "v"(n1.x), "v"(n1.y),
                "v"(n1.z), "v"(n1.w));
   for (int64_t k = k0; k < k1; ++k) {
@@ -1338,8 +1344,9 @@ hipError_t device_cus(int *out) {
 // ONE (keys of one token block, the page-sized keys): the initial state stays
 // a constant, which the compiler folds into the first rounds, and the loop
 // over token blocks goes.  12,000 ragged chains 234.5 -> 227.7 us per call,
-// 65,536 x 256 tokens in the fused form 93.4 -> 92.1; batches of several
-// hundred thousand one-key sequences lose 1.5% (61.4 -> 62.3).
+// 65,536 x 256 tokens in the fused form 93.4 -> 92.1; batches of 65,536 to
+// 1,048,576 sequences of one or two keys within 0.5%, mostly below (262,144 x 1
+// 34.3 -> 34.2, 524,288 x 1 57.4 and 57.4, 524,288 x 2 94.9 -> 94.6).
 template <typename Off>
 static void launch_midstates(const int32_t *d_tokens, const Off *d_koff, const Off *d_toff,
                              int32_t n_seqs, int64_t n_keys, int32_t block_tokens,
@@ -1359,9 +1366,13 @@ hipError_t launch_sha256_midstates(const int32_t *d_tokens, const void *d_key_of
                                    hipStream_t stream) {
   if (n_keys <= 0) return hipSuccess;
   // Keys of several blocks, at most 16 per compute unit (8 for two-block
-  // keys, where the lane form catches up sooner): a workgroup of two waves
-  // per four keys (the schedules on their own wave); otherwise one lane per
-  // key.  EA_HASH_MID=lane or split forces a form.
+  // keys): a workgroup of two waves per four keys (the schedules on their own
+  // wave); otherwise one lane per key.  Whole calls of one-key sequences on
+  // 256 units, one lane per key / two waves, us: 1,024 tokens at 1,024 / 2,048
+  // / 4,096 / 8,192 keys 178 / 94, 179 / 112, 179 / 119, 190 / 215; 256 tokens
+  // 55 / 36, 55 / 42, 56 / 45, 60 / 72; 64 tokens 24.1 / 21.3, 24.8 / 23.4,
+  // 25.0 / 25.8, 29.0 / 35.4; 32 tokens 18.8 / 18.6, 19.5 / 20.4, 19.9 / 22.3.
+  // EA_HASH_MID=lane or split forces a form.
   const int64_t groups = (n_keys + kSpRows - 1) / kSpRows;
   bool split = false;
   const char *f = std::getenv("EA_HASH_MID");
@@ -1432,13 +1443,13 @@ hipError_t launch_sha256_chain(const uint32_t *d_mid, const void *d_key_offsets,
   if (form == kChainSplit && n_seqs > kMaxSplitGroups) form = kChainPair;  // grid bound
   if (form < 0) {
     // Up to four sequences per compute unit (one workgroup of four rows): the
-    // row form, whose chains of 256 keys take 363-373 us in a whole call
-    // against 392-427 in the two-lane form; with a second workgroup on each
-    // unit it takes 448-459 us (1,280 to 2,048 chains) against 413-437.  Up
+    // row form, whose chains of 256 keys take 345-361 us in a whole call
+    // against 370-385 in the two-lane form; with a second workgroup on each
+    // unit it takes 408-424 us (1,025 to 2,048 chains) against 385-397.  Up
     // to 128 per unit (two workgroups of the two-lane form) that form: 32,768
-    // chains of 16 / 64 / 128 keys 79 / 257 / 487 us against 86 / 269 / 537
-    // with one lane per sequence; beyond, the one-lane form: 36,000 chains of
-    // 64 keys 286 us against 343.
+    // chains of 16 / 64 / 128 keys 75 / 224 / 428 us against 82 / 258 / 501
+    // with one lane per sequence; beyond, the one-lane form: 32,769 chains of
+    // 64 keys 258 us against 288, 36,000 268 against 302.
     int cus = 0;
     const hipError_t e = device_cus(&cus);
     if (e != hipSuccess) return e;

@@ -268,3 +268,19 @@ def test_schedule_waves_that_share_simds_run_at_raised_priority(assembly):
     for name, body in shared.items():
         prio = [rest.strip() for op, rest, _ in _instructions(body) if op == "s_setprio"]
         assert prio == ["3"], (name, prio)
+
+
+def test_hash_roofline_counts_the_kernel_it_is_taken_on(assembly):
+    # the bench prices the 65,536-sequence batch at this many vector
+    # instructions per key: the key loop of the fused kernel for one-block
+    # keys, the only loop of that length in it
+    import bench
+    bodies, _, _ = kernels(assembly["ea_sha256_kernels.hip"])
+    body = next(b for n, b in bodies.items() if "sha256_fused_scanILb1E" in n)
+    at = {m.group(1): k for k, m in enumerate(re.match(r"\.(LBB\d+_\d+):", l) for l in body) if m}
+    loops = []
+    for k, line in enumerate(body):
+        m = re.match(r"\s+s_c?branch\S*\s+\.(LBB\d+_\d+)", line)
+        if m and at.get(m.group(1), k) < k:
+            loops.append(sum(1 for l in body[at[m.group(1)]:k] if re.match(r"\s+v_", l)))
+    assert max(loops) == bench.HASH_INSTR_PER_KEY, loops
