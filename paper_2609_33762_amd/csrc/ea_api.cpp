@@ -559,16 +559,20 @@ ea::PieceCopy base_copy(const ea_cache *c, int64_t slot_bytes, int32_t chunk) {
 constexpr int32_t kTwinLayers = 8;
 
 // Layers whose scale words one unit moves (PieceCopy::scale_layers) in a copy
-// of all layers.  Reads of the slots gain by eight at a time, layered loads
-// most (4,096 pages of 4 KiB pieces 310.6 us a layer -> 302.1, of 16 KiB
-// 1,184.8 -> 1,175.9; 400 pages of 48 layers in 4 KiB pieces loaded at once
-// 1,454 -> 1,435).  Stores over the host link gain with pieces of up to 2 KiB
-// (400 pages of 48 x 1 KiB 685 -> 640 us, of 2 KiB 797 -> 750) and lose above,
-// where the 64-byte write comes in between long runs of the pieces' own (of 3
-// KiB 1,098 -> 1,136, of 8 KiB 2,855 -> 2,912, of 16 KiB 5,649 -> 5,773).
-int32_t scale_group(int64_t chunk, int64_t piece, int dir, int route) {
+// of all layers, `total` bytes of pieces.  Reads of the slots gain by eight at
+// a time, layered loads most (4,096 pages of 4 KiB pieces 310.6 us a layer ->
+// 302.1, of 16 KiB 1,184.8 -> 1,175.9; 400 pages of 48 layers in 4 KiB pieces
+// loaded at once 1,454 -> 1,435).  Stores over the host link gain with pieces
+// of up to 2 KiB (400 pages of 48 x 1 KiB 685 -> 640 us, of 2 KiB 797 -> 750)
+// and, larger, while the call is latency (8 pages of 24 x 4 KiB 24.8 -> 24.4
+// us, of 48 x 4 KiB 44.8 -> 43.6, 33 of 24 x 4 KiB 82.3 -> 80.8); beyond they
+// lose, as the 64-byte write comes in between long runs of the pieces' own (33
+// pages of 48 x 4 KiB, 6.5 MB, 132.3 -> 134.4, of 8 KiB 247.9 -> 251.8, 400 of 48
+// x 3 KiB 1,098 -> 1,136, of 8 KiB 2,855 -> 2,912, of 16 KiB 5,649 -> 5,773).
+int32_t scale_group(int64_t chunk, int64_t piece, int64_t total, int dir, int route) {
   if (chunk != 1) return 1;
-  return dir == ea::kToSlots && route == ea::kRouteHostLink && piece > 2048 ? 1 : 8;
+  const bool store = dir == ea::kToSlots && route == ea::kRouteHostLink;
+  return store && piece > 2048 && total > (int64_t(5) << 20) ? 1 : 8;
 }
 
 // Launch a piece copy for n (slot, page) entries, one per page (slots null:
@@ -580,7 +584,8 @@ int launch_entries(ea::PieceCopy a, IndexRing &ring, const int64_t *slots,
                    const int32_t *pages, int64_t n, int dir, int route, int64_t grid,
                    hipStream_t s) {
   a.n = n;
-  a.scale_layers = scale_group(a.chunk, a.piece_bytes, dir, route);
+  a.scale_layers =
+      scale_group(a.chunk, a.piece_bytes, n * a.layer_count * a.piece_bytes, dir, route);
   if (route == ea::kRouteHbm) {
     // page ids in the arguments and units in entry order: parts may be used
     const bool parts = !slots && !a.layer_major &&
@@ -1179,7 +1184,8 @@ int ea_load_blocks_layered(ea_tier *t, ea_cache *c, const int64_t *host_slots,
     a.xcd_mask = t->xcd_load;
     a.n = m;
     a.layer_count = 1;
-    a.scale_layers = scale_group(t->chunk, t->piece, ea::kToPages, ea::kRouteHostLink);
+    a.scale_layers = scale_group(t->chunk, t->piece, m * c->page, ea::kToPages,
+                                 ea::kRouteHostLink);
     ea::InlineIdx inl;
     const ea::InlineIdx *pin = nullptr;
     IndexRing &ring = t->res[EA_DIR_LOAD].ring;

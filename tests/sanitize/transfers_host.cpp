@@ -290,14 +290,17 @@ int main() {
     if (g_allocations != allocations) fail("allocated again", 40);
     if (g_from_device != before + (layers >= 8 ? 3 * layers : 0)) fail("indices copied", layers);
   }
-  // pieces of 2,048 bytes and the next larger ones; layers around the groups'
-  // ends; one page per slot, and chunks, whose words are not neighbours
+  // layers around the groups' ends; one page per slot, and chunks, whose words
+  // are not neighbours
   for (int32_t layers : {1, 7, 8, 9, 17})
     for (int32_t n : {3, 40}) {
-      scale_words(layers, 64, 1, n, 8, 8);
-      scale_words(layers, 65, 1, n, 1, 8);
+      scale_words(layers, 65, 1, n, 8, 8);
       scale_words(layers, 2, 16, n, 1, 1);
     }
+  // stores of pieces of 2,048 bytes and the next larger ones, around 5 MiB
+  scale_words(17, 64, 1, 200, 8, 8);
+  scale_words(17, 65, 1, 148, 8, 8);
+  scale_words(17, 65, 1, 149, 1, 8);
   if (!g_device.empty()) fail("device memory left", 0);
   std::puts("ok");
   return 0;
