@@ -1631,9 +1631,10 @@ def summarize_plans(d):
         counters = {label: os.path.join(base, label, f"{label}_counter_collection.csv")
                     for label in ("fetch", "write")}
         if not all(os.path.exists(f) for f in counters.values()):
-            lines += ["", "Byte counters: not collected for this plan in this retake (its "
+            lines += ["", "Byte counters: not collected for this plan (on earlier kernels its "
                       "FETCH_SIZE pass stopped with a segmentation fault in host code, inside "
-                      "the profiler's interception of the plan's own runtime calls).", ""]
+                      "the profiler's interception of the plan's own runtime calls, and it "
+                      "has not been run since).", ""]
             continue
         tot = {}
         for label, ctr in (("fetch", "FETCH_SIZE"), ("write", "WRITE_SIZE")):
